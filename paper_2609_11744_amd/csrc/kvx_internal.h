@@ -46,16 +46,24 @@ constexpr uint32_t kPartThreads = 256;
 // Scatters of at least this many blocks run in destination order.
 constexpr int32_t kOrderedScatterMinBlocks = 1024;
 
-// Workgroups per slab for the layout (4 KiB pieces with the default layout,
-// heads with the reordering ones), and log2 of that count when it is a power
-// of two (else 32: the kernels divide).
-void slab_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift);
+// Pieces of a slab, in which calls are counted and reported (4 KiB pieces with
+// the default layout, heads with the reordering ones).
+uint32_t slab_pieces(int layout, uint32_t n16, uint32_t heads);
+
+// The layout a cache is copied as: HND with one head or one token per block is
+// the default layout byte for byte.
+int copy_layout(int layout, int32_t heads, int32_t block_size);
+
+// Workgroups per slab for a copy_layout (4 KiB each with the default layout and
+// HND, a head each with paged attention), and log2 of that count when it is a
+// power of two (else 32: the kernels divide).
+void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift);
 
 // How a gather or scatter walks its work items: the launcher's choice, also
 // reported by kvx_copy_walk (kvx_walk.cpp).
 struct Walk {
-  uint32_t parts = 0, parts_shift = 32;  // workgroups per slab (slab_parts)
-  uint32_t n_work = 0;                    // work items (workgroups) of the call
+  uint32_t pieces = 0;                    // pieces per slab (slab_pieces)
+  uint32_t parts = 0, parts_shift = 32;  // workgroups per slab (copy_parts)
   uint32_t pair_shift = 32;               // ordered scatter: fronts 2^pair_shift slices apart
   uint32_t gather_pair_shift = 32;        // gather: slices paired 2^gather_pair_shift apart
   bool linear = false;                    // workgroup b moves work item b
@@ -63,7 +71,7 @@ struct Walk {
 };
 
 // The walk of a validated gather (to_packed) or scatter: KVX_EINTERNAL when
-// its work items do not fit 31 bits.
+// its slabs' pieces do not fit 31 bits.
 kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g, Walk* w);
 
 

@@ -106,6 +106,12 @@ struct SlabGeom {
   uint32_t x;      // elements per 16-byte vector: 16 / elem_bytes
   uint32_t nh;     // vectors of one head: bs * v16
   uint32_t prow;   // packed row stride in vectors: heads * v16
+  // HND: destination vector w of a slab is (w / outer, rest / v16, rest % v16)
+  // = (a, b, dv) and comes from source vector a * v16 + b * src_step + dv
+  // (gather: a token, b head; scatter: a head, b token).
+  FastDiv outer;
+  uint32_t src_step;
+
   FastDiv pad;       // scatter: LDS pad period (see lds_slot)
   uint32_t v_pairs;  // paged-attention V of 2-byte words gathered as row pairs (v_pairs_gather)
   uint32_t swz;      // gather: LDS swizzle shift (see lds_slot)
@@ -134,6 +140,7 @@ struct UnitGeom {
   uint32_t bpc;
   uint32_t n_blocks;
   uint32_t num_blocks;       // pool size
+  uint32_t n_units;
   uint32_t n16;              // 16-byte vectors per slab
   uint32_t parts;            // workgroups per slab (parts_shift: log2 of a power of two, else 32)
   uint32_t parts_shift;
@@ -304,22 +311,22 @@ __device__ __forceinline__ uint32_t packed_at(uint32_t w, const SlabGeom& g) {
   return t * g.prow + dv;
 }
 
-// HND: local vector w is cache vector w and local packed vector w.
-template <bool kToPacked, int T, int V>
-__device__ __forceinline__ void move_head_rows(const v4u* __restrict__ src, v4u* __restrict__ dst,
-                                               const SlabGeom& g) {
-  v4u r[V];
-#pragma unroll
-  for (int q = 0; q < V; ++q) {
-    const uint32_t w = threadIdx.x + q * T;
-    if (w < g.nh) r[q] = __builtin_nontemporal_load(src + (kToPacked ? w : packed_at(w, g)));
-  }
-  const auto out = stream_dst(dst, head_dst_bytes<kToPacked>(g));
-#pragma unroll
-  for (int q = 0; q < V; ++q) {
-    const uint32_t w = threadIdx.x + q * T;
-    if (w < g.nh) store_stream(out, kToPacked ? packed_at(w, g) : w, r[q]);
-  }
+// HND: source vector of destination vector w of a slab.
+__device__ __forceinline__ uint32_t hnd_source(uint32_t w, const SlabGeom& g) {
+  uint32_t rest, dv;
+  const uint32_t a = divmod(w, g.outer, rest);
+  const uint32_t b = divmod(rest, g.v16, dv);
+  return a * g.v16.d + b * g.src_step + dv;
+}
+
+// HND: move piece `part` of a slab: 256 consecutive vectors of the destination
+// (fewer in a slab's last piece).
+template <int T>
+__device__ __forceinline__ void move_rows(const v4u* __restrict__ src, v4u* __restrict__ dst,
+                                          uint32_t n16, const SlabGeom& g, uint32_t part) {
+  const uint32_t w = part * T + threadIdx.x;
+  const auto out = stream_dst(dst, n16 * 16u);
+  if (w < n16) store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
 }
 
 // Load the head's nh source vectors, in source order, into the padded LDS
@@ -477,10 +484,6 @@ __device__ __forceinline__ void move_head(const v4u* __restrict__ src, v4u* __re
       typename std::conditional<kElem == 2, uint16_t,
                                 typename std::conditional<kElem == 4, uint32_t,
                                                           uint64_t>::type>::type>::type E;
-  if (kLayout == KVX_LAYOUT_HND) {
-    move_head_rows<kToPacked, T, V>(src, dst, g);
-    return;
-  }
   stage_in<kToPacked, T, V>(src, g);
   __syncthreads();
   const v4u* lds = reinterpret_cast<const v4u*>(kvx_lds);
@@ -495,7 +498,7 @@ __device__ __forceinline__ void move_head(const v4u* __restrict__ src, v4u* __re
 }
 
 // Move part `part` of one slab in the direction and layout of the kernel: a
-// 4 KiB piece with the default layout, one head with the reordering ones.
+// 4 KiB piece with the default layout and HND, one head with paged attention.
 template <bool kToPacked, int kLayout, int kElem, int T, int V>
 __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, const SlabGeom& g,
                                           uint32_t kv, uint32_t part) {
@@ -509,6 +512,11 @@ __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, c
       move_slab<T, V>(pv + off, kv4 + off, n);
     else
       move_slab<T, V>(kv4 + off, pv + off, n);
+  } else if (kLayout == KVX_LAYOUT_HND) {
+    if (kToPacked)
+      move_rows<T>(pv, kv4, n16, g, part);
+    else
+      move_rows<T>(kv4, pv, n16, g, part);
   } else {
     v4u* cache_head = pv + part * g.nh;       // head `part`: nh contiguous cache vectors
     v4u* packed_head = kv4 + part * g.v16.d;  // its first packed row
@@ -541,7 +549,7 @@ __device__ __forceinline__ uint32_t split_work(uint32_t w, uint32_t parts, uint3
 template <bool kToPacked, bool kOrdered, int kLayout, int kElem, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_units_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table, UnitGeom g,
-                      uint32_t work_base, uint32_t work_count,
+                      uint32_t unit_base, uint32_t part_base, uint32_t work_count,
                       const OrderEntry* __restrict__ order, char* __restrict__ packed,
                       int* __restrict__ err) {
   uint32_t part;
@@ -549,7 +557,8 @@ __global__ void __launch_bounds__(T)
                      : kOrdered && g.pair_shift < 32 ? xcd_two_fronts(blockIdx.x, work_count,
                                                                       g.parts_shift)
                                                      : xcd_contiguous(blockIdx.x, work_count);
-  uint32_t u = split_work(work_base + w, g.parts, g.parts_shift, g.parts_div, &part);
+  uint32_t u =
+      unit_base + split_work(part_base + w, g.parts, g.parts_shift, g.parts_div, &part);
   uint32_t c, first, nc, lk, j;
   int32_t id;
   char* layer;
@@ -634,11 +643,12 @@ struct ChunkGeom {
 template <bool kToPacked, int kLayout, int kElem, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_chunks_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
-                       const kvx_chunk_ref* __restrict__ refs, ChunkGeom g, uint32_t work_base,
-                       uint32_t work_count, char* __restrict__ packed, int* __restrict__ err) {
+                       const kvx_chunk_ref* __restrict__ refs, ChunkGeom g, uint32_t unit_base,
+                       uint32_t part_base, uint32_t work_count, char* __restrict__ packed, int* __restrict__ err) {
   uint32_t part;
-  const uint32_t u = split_work(work_base + xcd_contiguous(blockIdx.x, work_count), g.parts,
-                                g.parts_shift, g.parts_div, &part);
+  const uint32_t u =
+      unit_base + split_work(part_base + xcd_contiguous(blockIdx.x, work_count), g.parts,
+                             g.parts_shift, g.parts_div, &part);
   const uint32_t c = divu(u, g.upc_div);
   const uint32_t r = u - c * g.upc;
   const uint32_t lk = divu(r, g.bpc_div);
@@ -783,7 +793,8 @@ inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, kPartThreads, 1>), \
                          grid, dim3(kPartThreads), 0, stream, __VA_ARGS__);            \
     else if (layout == KVX_LAYOUT_HND)                                                 \
-      KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, __VA_ARGS__);                 \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, kPartThreads, 1>), \
+                         grid, dim3(kPartThreads), 0, stream, __VA_ARGS__);            \
     else if (elem == 1)                                                                \
       KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, __VA_ARGS__);          \
     else if (elem == 2)                                                                \
@@ -794,35 +805,46 @@ inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
       KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, __VA_ARGS__);          \
   } while (0)
 
-template <bool kToPacked, bool kOrdered>
-hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug, uint32_t n_work,
-                  const OrderEntry* order, char* packed, int* err, int layout, int elem,
-                  hipStream_t stream) {
-  const SlabGeom& sg = ug.sg;
-  for (uint32_t base = 0; base < n_work; base += kMaxWorkPerLaunch) {
-    const uint32_t cnt = n_work - base < kMaxWorkPerLaunch ? n_work - base : kMaxWorkPerLaunch;
-    const dim3 grid(cnt);
-    KVX_DISPATCH(copy_units_kernel, (kToPacked, kOrdered), lp, bt, ug, base, cnt,
-                 order, packed, err);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+// Calls launch(unit_base, part_base, workgroups) for each launch of a copy of
+// n_units slabs of `parts` workgroups each: as many whole slabs as fit
+// kMaxWorkPerLaunch, or runs of one slab's parts where a slab has more.
+template <typename F>
+hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
+  const uint32_t units = parts < kMaxWorkPerLaunch ? kMaxWorkPerLaunch / parts : 1;
+  for (uint64_t u = 0; u < n_units; u += units) {
+    const uint32_t nu = n_units - u < units ? (uint32_t)(n_units - u) : units;
+    const uint64_t work = (uint64_t)nu * parts;
+    for (uint64_t p = 0; p < work; p += kMaxWorkPerLaunch) {
+      launch((uint32_t)u, (uint32_t)p,
+             (uint32_t)(work - p < kMaxWorkPerLaunch ? work - p : kMaxWorkPerLaunch));
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }
 
+template <bool kToPacked, bool kOrdered>
+hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
+                  const OrderEntry* order, char* packed, int* err, int layout, int elem,
+                  hipStream_t stream) {
+  const SlabGeom& sg = ug.sg;
+  return each_launch(ug.n_units, ug.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
+    const dim3 grid(cnt);
+    KVX_DISPATCH(copy_units_kernel, (kToPacked, kOrdered), lp, bt, ug, unit, part, cnt,
+                 order, packed, err);
+  });
+}
+
 template <bool kToPacked>
 hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_ref* refs,
-                         const ChunkGeom& cg, uint32_t n_work, char* packed, int* err,
+                         const ChunkGeom& cg, uint32_t n_units, char* packed, int* err,
                          int layout, int elem, hipStream_t stream) {
   const SlabGeom& sg = cg.sg;
-  for (uint32_t base = 0; base < n_work; base += kMaxWorkPerLaunch) {
-    const uint32_t cnt = n_work - base < kMaxWorkPerLaunch ? n_work - base : kMaxWorkPerLaunch;
+  return each_launch(n_units, cg.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
-    KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, base, cnt, packed, err);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+    KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, unit, part, cnt, packed, err);
+  });
 }
 
 DivU32 div_u32(uint32_t d) {
@@ -838,7 +860,7 @@ DivU32 div_u32(uint32_t d) {
 FastDiv fast_div(uint32_t d) {
   FastDiv f;
   f.d = d;
-  f.m = d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
+  f.m = d <= 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
   return f;
 }
 
@@ -860,6 +882,8 @@ SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   sg.x = x;
   sg.nh = bs * v16;
   sg.prow = h * v16;
+  sg.outer = fast_div(to_packed ? sg.prow : sg.nh);
+  sg.src_step = to_packed ? sg.nh : sg.prow;
   // V of 2-byte words as row pairs in a gather: token pairs, so an even
   // block size (v_pairs_gather says why not in a scatter)
   sg.v_pairs = c->elem_bytes == 2 && to_packed && bs % 2 == 0 ? 1u : 0u;
@@ -931,8 +955,10 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   ug.bpc = (uint32_t)g.bpc;
   ug.n_blocks = (uint32_t)g.n_blocks;
   ug.num_blocks = (uint32_t)g.num_blocks;
+  ug.n_units = (uint32_t)g.n_units;
   ug.n16 = (uint32_t)(g.slab / 16);
-  const int layout = cache->layout, elem = cache->elem_bytes;
+  const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
+  const int elem = cache->elem_bytes;
   ug.parts = walk.parts;
   ug.parts_shift = walk.parts_shift;
   ug.parts_div = div_u32(ug.parts);
@@ -942,7 +968,6 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   ug.nb_div = div_u32(ug.n_blocks);
   ug.slab = (uint64_t)g.slab;
   ug.sg = slab_geom(cache, to_packed);
-  const uint32_t n_work = walk.n_work;
   const uint32_t n_slices = (uint32_t)(2 * g.lr);
   ug.pair_shift = walk.pair_shift;
   ug.gather_pair_shift = walk.gather_pair_shift;
@@ -950,8 +975,8 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   ug.linear_walk = walk.linear ? 1u : 0u;
   ug.xcd_slices_div = div_u32(n_slices / kXcds ? n_slices / kXcds : 1);
   if (to_packed) {
-    hipError_t e = launch<true, false>(lp, block_table, ug, n_work, nullptr, (char*)packed, err,
-                                       layout, elem, stream);
+    hipError_t e = launch<true, false>(lp, block_table, ug, nullptr, (char*)packed, err, layout,
+                                       elem, stream);
     return e == hipSuccess ? KVX_OK : KVX_EHIP;
   }
   // Destination-ordered scatter for large calls of multi-block chunks; the
@@ -974,15 +999,15 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
                        (uint32_t)g.n_blocks, (uint32_t)g.num_blocks, order);
     e = hipGetLastError();
     if (e == hipSuccess)
-      e = launch<false, true>(lp, block_table, ug, n_work, order, (char*)packed, err, layout,
-                              elem, stream);
+      e = launch<false, true>(lp, block_table, ug, order, (char*)packed, err, layout, elem,
+                              stream);
     if (own) {
       const hipError_t ef = hipFreeAsync(order, stream);
       if (e == hipSuccess) e = ef;
     }
   } else {
-    e = launch<false, false>(lp, block_table, ug, n_work, nullptr, (char*)packed, err, layout,
-                             elem, stream);
+    e = launch<false, false>(lp, block_table, ug, nullptr, (char*)packed, err, layout, elem,
+                             stream);
   }
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
@@ -1011,8 +1036,9 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.lr2 = (uint32_t)(2 * (l1 - l0));
   cg.num_blocks = (uint32_t)cache->num_blocks;
   cg.n16 = (uint32_t)(slab / 16);
-  const int layout = cache->layout, elem = cache->elem_bytes;
-  slab_parts(layout, cg.n16, (uint32_t)cache->num_kv_heads, &cg.parts, &cg.parts_shift);
+  const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
+  const int elem = cache->elem_bytes;
+  copy_parts(layout, cg.n16, (uint32_t)cache->num_kv_heads, &cg.parts, &cg.parts_shift);
   cg.parts_div = div_u32(cg.parts);
   cg.upc_div = div_u32(cg.upc);
   cg.bpc_div = div_u32(cg.bpc);
@@ -1020,11 +1046,9 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.slab = (uint64_t)slab;
   cg.packed_bytes = packed_bytes;
   cg.sg = slab_geom(cache, to_packed);
-  if ((uint64_t)n_units * cg.parts > 0x7FFFFFFF) return KVX_EINTERNAL;
-  const uint32_t n_work = (uint32_t)n_units * cg.parts;
-  hipError_t e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, n_work,
+  hipError_t e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, (uint32_t)n_units,
                                                  (char*)packed, err, layout, elem, stream)
-                           : launch_chunks<false>(lp, block_table, refs, cg, n_work,
+                           : launch_chunks<false>(lp, block_table, refs, cg, (uint32_t)n_units,
                                                   (char*)packed, err, layout, elem, stream);
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }

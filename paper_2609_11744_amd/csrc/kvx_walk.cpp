@@ -2,6 +2,7 @@
 // work items are laid out over the chip's XCDs, whether a scatter visits its
 // destinations in ascending order, and which slices move together. The launcher
 // (kvx_kernels.hip) and kvx_copy_walk share it.
+#include <algorithm>
 #include <cstdint>
 
 #include "kvx.h"
@@ -9,8 +10,17 @@
 
 namespace kvx {
 
-void slab_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift) {
-  *parts = layout == KVX_LAYOUT_NHD ? (n16 + kPartThreads - 1) / kPartThreads : heads;
+uint32_t slab_pieces(int layout, uint32_t n16, uint32_t heads) {
+  return layout == KVX_LAYOUT_NHD ? (n16 + kPartThreads - 1) / kPartThreads : heads;
+}
+
+int copy_layout(int layout, int32_t heads, int32_t block_size) {
+  if (layout == KVX_LAYOUT_HND && (heads == 1 || block_size == 1)) return KVX_LAYOUT_NHD;
+  return layout;
+}
+
+void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift) {
+  *parts = layout == KVX_LAYOUT_PAGED_ATTN ? heads : (n16 + kPartThreads - 1) / kPartThreads;
   *shift = (*parts & (*parts - 1)) == 0 ? (uint32_t)__builtin_ctz(*parts) : 32u;
 }
 
@@ -91,7 +101,7 @@ uint32_t pairing_2mib(uint32_t parts_shift, uint32_t n_slices, uint32_t bpc, uin
 // 76.6 against 76.0 % and 74.4 against 73.7 %; 16 KiB slabs in 16-block chunks
 // (D = 8) 74.4 against 73.3 %. With 4 and 8 KiB slabs (D = 32, 16) they lost
 // 1.3-1.4 points, so smaller slabs keep D <= 4.
-uint32_t scatter_pairing(uint32_t n_work, uint32_t parts_shift, uint32_t n_slices, uint32_t bpc,
+uint32_t scatter_pairing(uint64_t n_work, uint32_t parts_shift, uint32_t n_slices, uint32_t bpc,
                          uint64_t slab) {
   if (n_work > kMaxWorkPerLaunch || n_slices % (2 * kXcds)) return 32;
   return pairing_2mib(parts_shift, n_slices, bpc, slab, slab > 8192 ? 4 : 2);
@@ -119,13 +129,18 @@ uint32_t gather_pairing(uint32_t parts_shift, uint32_t n_slices, uint32_t bpc, u
 kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g, Walk* w) {
   *w = Walk();
   if (g.n_units == 0) return KVX_OK;
-  const uint32_t n16 = (uint32_t)(g.slab / 16);
-  slab_parts(cache->layout, n16, (uint32_t)cache->num_kv_heads, &w->parts, &w->parts_shift);
-  if ((uint64_t)g.n_units * w->parts > 0x7FFFFFFF) return KVX_EINTERNAL;
-  w->n_work = (uint32_t)g.n_units * w->parts;
+  const uint32_t n16 = (uint32_t)(g.slab / 16), heads = (uint32_t)cache->num_kv_heads;
+  w->pieces = slab_pieces(cache->layout, n16, heads);
+  if ((uint64_t)g.n_units * w->pieces > 0x7FFFFFFF) return KVX_EINTERNAL;
+  copy_parts(copy_layout(cache->layout, cache->num_kv_heads, cache->block_size), n16, heads,
+             &w->parts, &w->parts_shift);
+  const uint64_t n_work = (uint64_t)g.n_units * w->parts;
+  // Pairs are chosen where both the pieces and the workgroups of a slab are a
+  // power of two.
+  const uint32_t pair_parts = w->pieces & (w->pieces - 1) ? 32u : w->parts_shift;
   const uint32_t n_slices = (uint32_t)(2 * g.lr);
   if (to_packed) {
-    w->gather_pair_shift = gather_pairing(w->parts_shift, n_slices, (uint32_t)g.bpc,
+    w->gather_pair_shift = gather_pairing(pair_parts, n_slices, (uint32_t)g.bpc,
                                           (uint64_t)g.slab);
     return KVX_OK;
   }
@@ -133,8 +148,8 @@ kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g
   w->ordered = scatter_in_destination_order(g.n_blocks, g.bpc, g.slab, cache->layout,
                                             cache->num_kv_heads);
   if (w->ordered)
-    w->pair_shift = scatter_pairing(w->n_work, w->parts_shift, n_slices, (uint32_t)g.bpc,
-                                    (uint64_t)g.slab);
+    w->pair_shift = scatter_pairing(std::max(n_work, (uint64_t)g.n_units * w->pieces), pair_parts,
+                                    n_slices, (uint32_t)g.bpc, (uint64_t)g.slab);
   return KVX_OK;
 }
 
@@ -153,10 +168,10 @@ extern "C" kvx_status kvx_copy_walk(const kvx_cache* cache, int32_t l0, int32_t 
     if (st != KVX_OK) return st;
     kvx::Walk w;
     st = kvx::choose_walk(to_packed == 1, cache, g, &w);
-    if (st != KVX_OK || w.n_work == 0) return st;
+    if (st != KVX_OK || w.pieces == 0) return st;
     const uint32_t ps = to_packed ? w.gather_pair_shift : w.pair_shift;
-    out->work_items = w.n_work;
-    out->parts = (int32_t)w.parts;
+    out->work_items = g.n_units * w.pieces;
+    out->parts = (int32_t)w.pieces;
     out->ordered = w.ordered ? 1 : 0;
     out->linear = w.linear ? 1 : 0;
     out->pair_slices = ps < 32 ? (int32_t)(1u << ps) : 0;
