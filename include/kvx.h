@@ -157,18 +157,20 @@ kvx_status kvx_scatter_blocks(const kvx_cache* cache, int32_t l0, int32_t l1,
 /* How kvx_gather_blocks (to_packed = 1) or kvx_scatter_blocks (0) with these
  * arguments walks its work: the launcher's own choice, reported for tests and
  * measurement records. Pure host code: the cache's tensor pointers may be
- * NULL. A call moves work_items workgroups; each moves one part of a slab
- * (parts per slab: 4 KiB pieces with the default layout, heads with the
- * others). A scatter of 1,024 blocks or more in chunks of more than one block
- * runs in ascending destination order (ordered = 1; block ids bucketed by a
- * small kernel first), except with slabs of at most 8 KiB in the default
- * layout (or a reordering layout with one KV head): those, like every smaller
- * scatter, walk
- * the packed image in order, with linear = 1 when workgroup b moves work item
- * b rather than each XCD taking one contiguous range. pair_slices = D > 0:
- * slices D apart, whose runs sit 2 MiB apart in a packed chunk, are moved
- * together (the gather's paired walk, or an ordered scatter's two fronts per
- * XCD: fronts = 2). For an empty call every field is 0. KVX_EINVAL for the
+ * NULL. A call moves work_items pieces of slabs, parts per slab (4 KiB pieces
+ * with the default layout, heads with the others); a workgroup moves one piece,
+ * or where pieces are small several, or a share of a large one. A scatter of
+ * 1,024 blocks or more in chunks of more than one block runs in ascending
+ * destination order (ordered = 1; block ids bucketed by a small kernel first),
+ * except with slabs of at most 8 KiB in the default layout (or a reordering
+ * layout with one KV head): those, like every smaller scatter, walk the packed
+ * image in order, with linear = 1 (slabs that divide 4 KiB or are a multiple
+ * of it) when the b-th workgroup moves the b-th share of the image rather than
+ * each XCD taking one contiguous range. pair_slices = D > 0: slices D apart,
+ * whose runs sit 2 MiB apart in a packed chunk, are moved together (the
+ * gather's paired walk, or an ordered scatter's two fronts per XCD: fronts =
+ * 2). For an
+ * empty call every field is 0. KVX_EINVAL for the
  * arguments the copy calls reject on the host (except pointers). */
 typedef struct kvx_walk {
   int64_t work_items;
@@ -190,8 +192,7 @@ kvx_status kvx_copy_walk(const kvx_cache* cache, int32_t l0, int32_t l1, int32_t
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): the same arguments, validation, kernels and result, but the
  * destination order that a scatter of 1,024 blocks or more computes first (in
- * chunks of more than one block, and with the default layout, or a
- * reordering layout with one KV head, only for slabs above 8 KiB) lives in
+ * chunks of more than one block; kvx_copy_walk says which are ordered) lives in
  * a fixed device array of the library's (512 KiB, KVX_NOALLOC_MAX_BLOCKS
  * 8-byte entries; each GPU the library runs on holds one until the process
  * ends) instead of stream-ordered scratch. The call allocates nothing.

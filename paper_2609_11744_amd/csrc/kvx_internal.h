@@ -59,6 +59,11 @@ int copy_layout(int layout, int32_t heads, int32_t block_size);
 // power of two (else 32: the kernels divide).
 void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift);
 
+// Slabs per workgroup for a copy_layout: 256 / n16 where at least two fit a
+// workgroup of one vector per thread, else 1.
+constexpr uint32_t kGroupMaxVectors = kPartThreads / 2;
+uint32_t copy_group(int layout, uint32_t n16);
+
 // How a gather or scatter walks its work items: the launcher's choice, also
 // reported by kvx_copy_walk (kvx_walk.cpp).
 struct Walk {

@@ -111,6 +111,8 @@ struct SlabGeom {
   // (gather: a token, b head; scatter: a head, b token).
   FastDiv outer;
   uint32_t src_step;
+  FastDiv n16;       // vectors per slab (used where slabs are grouped)
+  uint32_t piece;    // default layout and HND: vectors per workgroup (piece_vectors)
 
   FastDiv pad;       // scatter: LDS pad period (see lds_slot)
   uint32_t v_pairs;  // paged-attention V of 2-byte words gathered as row pairs (v_pairs_gather)
@@ -142,6 +144,7 @@ struct UnitGeom {
   uint32_t num_blocks;       // pool size
   uint32_t n_units;
   uint32_t n16;              // 16-byte vectors per slab
+  uint32_t group;            // slabs per workgroup (copy_unit_groups_kernel; else 1)
   uint32_t parts;            // workgroups per slab (parts_shift: log2 of a power of two, else 32)
   uint32_t parts_shift;
   // Ordered scatter walked as two fronts per XCD (xcd_two_fronts) whose
@@ -208,20 +211,12 @@ __device__ __forceinline__ uint32_t paired_slice(uint32_t r, DivU32 sx, uint32_t
   return ((jj >> ds) << (ds + 1)) + (jj & ((1u << ds) - 1)) + (h << ds);
 }
 
-template <int T, int V>
-__device__ __forceinline__ void move_slab(const v4u* __restrict__ s, v4u* __restrict__ d,
-                                          uint32_t n16) {
-  const auto out = stream_dst(d, n16 * 16u);
-  uint32_t i = threadIdx.x;
-  // Main body: V vectors per thread per pass, loads first.
-  for (; i + (V - 1) * T < n16; i += V * T) {
-    v4u r[V];
-#pragma unroll
-    for (int q = 0; q < V; ++q) r[q] = __builtin_nontemporal_load(s + i + q * T);
-#pragma unroll
-    for (int q = 0; q < V; ++q) store_stream(out, i + q * T, r[q]);
-  }
-  for (; i < n16; i += T) store_stream(out, i, __builtin_nontemporal_load(s + i));
+// One vector per thread: n is at most the workgroup's threads.
+__device__ __forceinline__ void move_piece(const v4u* __restrict__ s, v4u* __restrict__ d,
+                                           uint32_t n) {
+  const auto out = stream_dst(d, n * 16u);
+  if (threadIdx.x < n)
+    store_stream(out, threadIdx.x, __builtin_nontemporal_load(s + threadIdx.x));
 }
 
 // ---- cache layouts that reorder a slab ---------------------------------------
@@ -321,12 +316,12 @@ __device__ __forceinline__ uint32_t hnd_source(uint32_t w, const SlabGeom& g) {
 
 // HND: move piece `part` of a slab: 256 consecutive vectors of the destination
 // (fewer in a slab's last piece).
-template <int T>
 __device__ __forceinline__ void move_rows(const v4u* __restrict__ src, v4u* __restrict__ dst,
                                           uint32_t n16, const SlabGeom& g, uint32_t part) {
-  const uint32_t w = part * T + threadIdx.x;
+  const uint32_t w = part * g.piece + threadIdx.x;
+  const uint32_t end = (part + 1) * g.piece;
   const auto out = stream_dst(dst, n16 * 16u);
-  if (w < n16) store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
+  if (w < (end < n16 ? end : n16)) store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
 }
 
 // Load the head's nh source vectors, in source order, into the padded LDS
@@ -505,18 +500,18 @@ __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, c
   v4u* pv = reinterpret_cast<v4u*>(paged);
   v4u* kv4 = reinterpret_cast<v4u*>(pk);
   if (kLayout == KVX_LAYOUT_NHD) {
-    const uint32_t off = part * (uint32_t)(T * V);  // < n16: part < ceil(n16 / (T * V))
+    const uint32_t off = part * g.piece;  // < n16
     const uint32_t left = n16 - off;
-    const uint32_t n = left < (uint32_t)(T * V) ? left : (uint32_t)(T * V);
+    const uint32_t n = left < g.piece ? left : g.piece;
     if (kToPacked)
-      move_slab<T, V>(pv + off, kv4 + off, n);
+      move_piece(pv + off, kv4 + off, n);
     else
-      move_slab<T, V>(kv4 + off, pv + off, n);
+      move_piece(kv4 + off, pv + off, n);
   } else if (kLayout == KVX_LAYOUT_HND) {
     if (kToPacked)
-      move_rows<T>(pv, kv4, n16, g, part);
+      move_rows(pv, kv4, n16, g, part);
     else
-      move_rows<T>(kv4, pv, n16, g, part);
+      move_rows(kv4, pv, n16, g, part);
   } else {
     v4u* cache_head = pv + part * g.nh;       // head `part`: nh contiguous cache vectors
     v4u* packed_head = kv4 + part * g.v16.d;  // its first packed row
@@ -628,7 +623,9 @@ struct ChunkGeom {
   uint32_t bpc;
   uint32_t lr2;          // (l1 - l0) * 2
   uint32_t num_blocks;   // pool size
+  uint32_t n_units;      // n_chunks * upc
   uint32_t n16;
+  uint32_t group;        // slabs per workgroup, as in UnitGeom
   uint32_t parts;        // workgroups per slab, as in UnitGeom
   uint32_t parts_shift;
   DivU32 parts_div;
@@ -640,11 +637,19 @@ struct ChunkGeom {
   SlabGeom sg;
 };
 
+__device__ __forceinline__ bool chunk_ref_ok(const kvx_chunk_ref& ref, const ChunkGeom& g) {
+  return ref.n_blocks >= 1 && (uint32_t)ref.n_blocks <= g.bpc && ref.bt_offset >= 0 &&
+         (int64_t)ref.bt_offset + ref.n_blocks <= (int64_t)g.table_len &&
+         ref.packed_offset >= 0 && (ref.packed_offset & 15) == 0 &&
+         ref.packed_offset + (int64_t)g.lr2 * ref.n_blocks * (int64_t)g.slab <= g.packed_bytes;
+}
+
 template <bool kToPacked, int kLayout, int kElem, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_chunks_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
                        const kvx_chunk_ref* __restrict__ refs, ChunkGeom g, uint32_t unit_base,
-                       uint32_t part_base, uint32_t work_count, char* __restrict__ packed, int* __restrict__ err) {
+                       uint32_t part_base, uint32_t work_count, char* __restrict__ packed,
+                       int* __restrict__ err) {
   uint32_t part;
   const uint32_t u =
       unit_base + split_work(part_base + xcd_contiguous(blockIdx.x, work_count), g.parts,
@@ -654,12 +659,7 @@ __global__ void __launch_bounds__(T)
   const uint32_t lk = divu(r, g.bpc_div);
   const uint32_t j = r - lk * g.bpc;
   const kvx_chunk_ref ref = refs[c];
-  const bool ok = ref.n_blocks >= 1 && (uint32_t)ref.n_blocks <= g.bpc && ref.bt_offset >= 0 &&
-                  (int64_t)ref.bt_offset + ref.n_blocks <= (int64_t)g.table_len &&
-                  ref.packed_offset >= 0 && (ref.packed_offset & 15) == 0 &&
-                  ref.packed_offset + (int64_t)g.lr2 * ref.n_blocks * (int64_t)g.slab <=
-                      g.packed_bytes;
-  if (!ok) {
+  if (!chunk_ref_ok(ref, g)) {
     if (r == 0 && part == 0 && threadIdx.x == 0) atomicOr(err, kErrBadChunk);
     return;
   }
@@ -673,6 +673,159 @@ __global__ void __launch_bounds__(T)
   char* paged = layers.p[lk] + (uint64_t)(uint32_t)id * g.slab;
   char* pk = packed + ref.packed_offset + (uint64_t)(lk * nc + j) * g.slab;
   move_unit<kToPacked, kLayout, kElem, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
+}
+
+// ---- small slabs: several per workgroup ----------------------------------------
+//
+// A slab of at most kGroupMaxVectors vectors (2 KiB) would leave half of a
+// 256-thread workgroup or more idle, and the copy is then bound by the rate at
+// which workgroups are dispatched (1.65 per ns measured, so a slab each caps
+// 1 KiB slabs at 1.7 TB/s each way). So a workgroup moves `group` = 256 / n16
+// consecutive units, one vector per thread; thread t takes vector t % n16 of
+// unit t / n16. Where a slab is a whole number of waves (kWave) a wave's unit is
+// uniform and its decode stays on the scalar unit; else each lane decodes its
+// own. 1 GiB, 32 layers, gather / scatter, a slab per workgroup -> grouped:
+// 2 KiB slabs 373 / 378 -> 351 / 372 us, 1 KiB 641 / 588 -> 353 / 372 us,
+// 512 bytes 1272 / 1163 -> 366 / 384 us, 256 bytes 2540 / 2320 -> 370 / 384 us.
+// (128-thread workgroups holding half as many slabs measured level at 2 KiB
+// and 3 to 16 % slower at 1,536 and 1,280 bytes.)
+
+// Where one unit's slab lies, or ok = false: an id outside the pool (reported) or no unit.
+struct Place {
+  char* paged;
+  char* packed;
+  char* base;  // at or below this lane's destination, the same or nearby for the wave's lanes
+  bool ok;
+};
+
+// Store v at vector w of dst. Lanes of one wave may hold different dst; kWave
+// says that they do not. The streaming store takes one base per wave and a
+// 32-bit offset per lane, so lanes store relative to the first lane's `base`
+// where every lane is less than 4 GiB above it; otherwise (layers far apart in
+// one wave) with plain non-temporal stores.
+template <bool kWave>
+__device__ __forceinline__ void store_grouped(char* base, char* dst, uint32_t n16, uint32_t w,
+                                              v4u v) {
+  if (kWave) {
+    const auto out = stream_dst(reinterpret_cast<v4u*>(dst), n16 * 16u);
+    store_stream(out, w, v);
+    return;
+  }
+  const uint64_t b = (uint64_t)base;
+  const uint64_t b0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t off = (uint64_t)dst + 16u * w - b0;
+  if (__builtin_amdgcn_ballot_w64(off > 0xFFFFFFE0ull) == 0) {
+    const auto out = stream_dst(reinterpret_cast<v4u*>(b0), 0xFFFFFFFFu);
+    store_stream_at(out, (uint32_t)off, v);
+  } else {
+    __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(dst) + w);
+  }
+}
+
+// Unit of this thread in the workgroup, and its vector in the unit's slab.
+template <bool kWave>
+__device__ __forceinline__ uint32_t grouped_unit(const SlabGeom& g, uint32_t* w) {
+  uint32_t i = divmod(threadIdx.x, g.n16, *w);
+  return kWave ? (uint32_t)__builtin_amdgcn_readfirstlane((int)i) : i;
+}
+
+template <bool kToPacked, int kLayout, bool kWave>
+__device__ __forceinline__ void move_grouped(const Place& p, uint32_t w, const SlabGeom& g) {
+  const v4u* src = reinterpret_cast<const v4u*>(kToPacked ? p.paged : p.packed);
+  char* dst = kToPacked ? p.packed : p.paged;
+  const uint32_t from = kLayout == KVX_LAYOUT_HND ? hnd_source(w, g) : w;
+  store_grouped<kWave>(p.base, dst, g.n16.d, w, __builtin_nontemporal_load(src + from));
+}
+
+// Unit u of a grouped call in image order, or (kOrdered) slice by slice in the
+// order's ascending destinations.
+template <bool kToPacked, bool kOrdered>
+__device__ __forceinline__ Place place_unit(const LayerPtrs& layers, const int32_t* block_table,
+                                            const UnitGeom& g, uint32_t u, const OrderEntry* order,
+                                            char* packed, int* err, bool report) {
+  uint32_t lk;
+  int32_t id;
+  if (kOrdered) {
+    lk = divu(u, g.nb_div);
+    const OrderEntry e = order[u - lk * g.n_blocks];
+    const uint32_t c = divu(e.index, g.bpc_div), first = c * g.bpc;
+    const uint32_t left = g.n_blocks - first;
+    id = e.id;
+    u = c * g.units_per_chunk + lk * (left < g.bpc ? left : g.bpc) + e.index - first;
+  } else {
+    const uint32_t c = divu(u, g.upc_div), first = c * g.bpc;
+    const uint32_t r = u - c * g.units_per_chunk, left = g.n_blocks - first;
+    const bool full = left >= g.bpc;
+    lk = divu(r, full ? g.bpc_div : g.last_div);
+    id = block_table[first + r - lk * (full ? g.bpc : left)];
+  }
+  char* layer = layers.p[lk];
+  Place p;
+  p.ok = (uint32_t)id < g.num_blocks;
+  if (!p.ok && report) atomicOr(err, kErrBadBlock);
+  p.paged = layer + (uint64_t)(uint32_t)id * g.slab;
+  p.packed = packed + (uint64_t)u * g.slab;
+  p.base = kToPacked ? p.packed : layer;
+  return p;
+}
+
+template <bool kToPacked, bool kOrdered, int kLayout, bool kWave>
+__global__ void __launch_bounds__(kPartThreads)
+    copy_unit_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table, UnitGeom g,
+                            uint32_t group_base, uint32_t group_count,
+                            const OrderEntry* __restrict__ order, char* __restrict__ packed,
+                            int* __restrict__ err) {
+  uint32_t w;
+  const uint32_t i = grouped_unit<kWave>(g.sg, &w);
+  const uint32_t u = (group_base + (g.linear_walk ? blockIdx.x
+                                                  : xcd_contiguous(blockIdx.x, group_count))) *
+                         g.group + i;
+  if (i >= g.group || u >= g.n_units) return;
+  const Place p = place_unit<kToPacked, kOrdered>(layers, block_table, g, u, order, packed, err,
+                                                  w == 0);
+  if (p.ok) move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
+}
+
+// Unit u of a chunk list's padded unit space (copy_chunks_kernel).
+template <bool kToPacked>
+__device__ __forceinline__ Place place_chunk_unit(const LayerPtrs& layers,
+                                                  const int32_t* block_table,
+                                                  const kvx_chunk_ref* refs, const ChunkGeom& g,
+                                                  uint32_t u, char* packed, int* err,
+                                                  bool report) {
+  const uint32_t c = divu(u, g.upc_div), r = u - c * g.upc;
+  const uint32_t lk = divu(r, g.bpc_div), j = r - lk * g.bpc;
+  const kvx_chunk_ref ref = refs[c];
+  Place p = {};
+  if (!chunk_ref_ok(ref, g)) {
+    if (r == 0 && report) atomicOr(err, kErrBadChunk);
+    return p;
+  }
+  const uint32_t nc = (uint32_t)ref.n_blocks;
+  if (j >= nc) return p;
+  const int32_t id = block_table[ref.bt_offset + j];
+  char* layer = layers.p[lk];
+  p.ok = (uint32_t)id < g.num_blocks;
+  if (!p.ok && report) atomicOr(err, kErrBadBlock);
+  p.paged = layer + (uint64_t)(uint32_t)id * g.slab;
+  p.packed = packed + ref.packed_offset + (uint64_t)(lk * nc + j) * g.slab;
+  p.base = kToPacked ? packed : layer;
+  return p;
+}
+
+template <bool kToPacked, int kLayout, bool kWave>
+__global__ void __launch_bounds__(kPartThreads)
+    copy_chunk_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
+                             const kvx_chunk_ref* __restrict__ refs, ChunkGeom g,
+                             uint32_t group_base, uint32_t group_count, char* __restrict__ packed,
+                             int* __restrict__ err) {
+  uint32_t w;
+  const uint32_t i = grouped_unit<kWave>(g.sg, &w);
+  const uint32_t u = (group_base + xcd_contiguous(blockIdx.x, group_count)) * g.group + i;
+  if (i >= g.group || u >= g.n_units) return;
+  const Place p = place_chunk_unit<kToPacked>(layers, block_table, refs, g, u, packed, err, w == 0);
+  if (p.ok) move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
 
 // Destination order for a scatter: order[] lists the block-table indexes,
@@ -789,12 +942,13 @@ inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
 
 #define KVX_DISPATCH(KERNEL, PREFIX, ...)                                                   \
   do {                                                                                 \
+    const uint32_t threads = (sg.piece + 63u) & ~63u;                                  \
     if (layout == KVX_LAYOUT_NHD)                                                      \
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, kPartThreads, 1>), \
-                         grid, dim3(kPartThreads), 0, stream, __VA_ARGS__);            \
+                         grid, dim3(threads), hold, stream, __VA_ARGS__);            \
     else if (layout == KVX_LAYOUT_HND)                                                 \
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, kPartThreads, 1>), \
-                         grid, dim3(kPartThreads), 0, stream, __VA_ARGS__);            \
+                         grid, dim3(threads), hold, stream, __VA_ARGS__);            \
     else if (elem == 1)                                                                \
       KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, __VA_ARGS__);          \
     else if (elem == 2)                                                                \
@@ -804,6 +958,17 @@ inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
     else                                                                               \
       KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, __VA_ARGS__);          \
   } while (0)
+
+// LDS that a workgroup of a linear-walk scatter reserves, unused, so that six
+// of them run on a compute unit instead of eight: with less of the image in
+// flight the writes land on fewer blocks at a time. 80 layers, 2,048 blocks:
+// 4 KiB slabs 472 -> 463 us, 2 KiB 239 -> 233 us, 8 KiB 710 -> 696 us (1,500
+// blocks); seven per unit 469, 236, 706 us, five 468, 237 us, four 510, 259 us.
+// 32 layers: 4 KiB 361 -> 359 us, 2 KiB level. Slabs below 1 KiB, whose lanes
+// each wait for a block id of their own, lost 1 to 2 %, so they run unheld; so
+// do the ordered walks and the gathers (4 to 5 % slower held to six).
+constexpr size_t kLinearScatterLds = 26624;
+constexpr uint32_t kHeldMinVectors = 64;
 
 // Calls launch(unit_base, part_base, workgroups) for each launch of a copy of
 // n_units slabs of `parts` workgroups each: as many whole slabs as fit
@@ -824,10 +989,37 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
   return hipSuccess;
 }
 
+// Launch the grouped kernel K<..., layout, kWave> of a copy of slabs of n16 vectors.
+#define KVX_LAUNCH_GROUPS(KERNEL, PREFIX, N16, ...)                                          \
+  do {                                                                                 \
+    const dim3 tb(kPartThreads);                                                       \
+    const bool wave = (N16) % 64 == 0;                                                 \
+    if (layout == KVX_LAYOUT_NHD && wave)                                              \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, true>), grid, tb, hold, stream, \
+                         __VA_ARGS__);                                                 \
+    else if (layout == KVX_LAYOUT_NHD)                                                 \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, false>), grid, tb, hold, stream, \
+                         __VA_ARGS__);                                                 \
+    else if (wave)                                                                     \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, true>), grid, tb, hold, stream, \
+                         __VA_ARGS__);                                                 \
+    else                                                                               \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, false>), grid, tb, hold, stream, \
+                         __VA_ARGS__);                                                 \
+  } while (0)
+
 template <bool kToPacked, bool kOrdered>
 hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
                   const OrderEntry* order, char* packed, int* err, int layout, int elem,
                   hipStream_t stream) {
+  const size_t hold =
+      !kToPacked && ug.linear_walk && ug.n16 >= kHeldMinVectors ? kLinearScatterLds : 0;
+  if (ug.group > 1)
+    return each_launch((ug.n_units - 1) / ug.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
+      const dim3 grid(cnt);
+      KVX_LAUNCH_GROUPS(copy_unit_groups_kernel, (kToPacked, kOrdered), ug.n16, lp, bt, ug, group,
+                        cnt, order, packed, err);
+    });
   const SlabGeom& sg = ug.sg;
   return each_launch(ug.n_units, ug.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
@@ -838,10 +1030,17 @@ hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
 
 template <bool kToPacked>
 hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_ref* refs,
-                         const ChunkGeom& cg, uint32_t n_units, char* packed, int* err,
-                         int layout, int elem, hipStream_t stream) {
+                         const ChunkGeom& cg, char* packed, int* err, int layout, int elem,
+                         hipStream_t stream) {
+  constexpr size_t hold = 0;
+  if (cg.group > 1)
+    return each_launch((cg.n_units - 1) / cg.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
+      const dim3 grid(cnt);
+      KVX_LAUNCH_GROUPS(copy_chunk_groups_kernel, (kToPacked), cg.n16, lp, bt, refs, cg, group,
+                        cnt, packed, err);
+    });
   const SlabGeom& sg = cg.sg;
-  return each_launch(n_units, cg.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
+  return each_launch(cg.n_units, cg.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, unit, part, cnt, packed, err);
   });
@@ -864,6 +1063,20 @@ FastDiv fast_div(uint32_t d) {
   return f;
 }
 
+// Vectors that a workgroup moves of a slab of n16 in the default layout or HND:
+// 256, or, where a second piece or a nearly empty third one would follow, the
+// slab in equal pieces of whole 128-byte lines, on as many waves as they need.
+// 1 GiB, 32 layers, gather: 4,352-byte slabs 459 us in 256s, 390 in halves,
+// 5 KiB 409 and 372, 6 KiB 381 and 353, 9 KiB in thirds 365 and 355; a fuller
+// third piece is better left short (10 KiB: 358 us in 256s, 366 in thirds), and
+// larger slabs measured level either way.
+uint32_t piece_vectors(uint32_t n16) {
+  const uint32_t parts = (n16 + kPartThreads - 1) / kPartThreads, last = n16 % kPartThreads;
+  if (parts == 1 || last == 0 || parts > 3 || (parts == 3 && last >= kPartThreads / 2))
+    return kPartThreads;
+  return ((n16 + parts - 1) / parts + 7u) & ~7u;
+}
+
 // Head shape and LDS layout for a reordering layout, from the stride (in
 // vectors) of the head's strided LDS reads: a gather (cache image in LDS)
 // reads paged-attention K vectors and V elements of consecutive dims at
@@ -882,6 +1095,8 @@ SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   sg.x = x;
   sg.nh = bs * v16;
   sg.prow = h * v16;
+  sg.piece = piece_vectors((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
+  sg.n16 = fast_div((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
   sg.outer = fast_div(to_packed ? sg.prow : sg.nh);
   sg.src_step = to_packed ? sg.nh : sg.prow;
   // V of 2-byte words as row pairs in a gather: token pairs, so an even
@@ -959,6 +1174,7 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   ug.n16 = (uint32_t)(g.slab / 16);
   const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
   const int elem = cache->elem_bytes;
+  ug.group = copy_group(layout, ug.n16);
   ug.parts = walk.parts;
   ug.parts_shift = walk.parts_shift;
   ug.parts_div = div_u32(ug.parts);
@@ -1035,10 +1251,12 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.bpc = (uint32_t)bpc;
   cg.lr2 = (uint32_t)(2 * (l1 - l0));
   cg.num_blocks = (uint32_t)cache->num_blocks;
+  cg.n_units = (uint32_t)n_units;
   cg.n16 = (uint32_t)(slab / 16);
   const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
   const int elem = cache->elem_bytes;
   copy_parts(layout, cg.n16, (uint32_t)cache->num_kv_heads, &cg.parts, &cg.parts_shift);
+  cg.group = copy_group(layout, cg.n16);
   cg.parts_div = div_u32(cg.parts);
   cg.upc_div = div_u32(cg.upc);
   cg.bpc_div = div_u32(cg.bpc);
@@ -1046,10 +1264,10 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.slab = (uint64_t)slab;
   cg.packed_bytes = packed_bytes;
   cg.sg = slab_geom(cache, to_packed);
-  hipError_t e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, (uint32_t)n_units,
-                                                 (char*)packed, err, layout, elem, stream)
-                           : launch_chunks<false>(lp, block_table, refs, cg, (uint32_t)n_units,
-                                                  (char*)packed, err, layout, elem, stream);
+  hipError_t e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, (char*)packed, err,
+                                                 layout, elem, stream)
+                           : launch_chunks<false>(lp, block_table, refs, cg, (char*)packed, err,
+                                                  layout, elem, stream);
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
 

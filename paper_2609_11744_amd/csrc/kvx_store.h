@@ -46,4 +46,9 @@ __device__ __forceinline__ void store_stream(const StreamDst& d, uint32_t i, v4u
   __builtin_amdgcn_raw_buffer_store_b128(v, d.rsrc, i * 16u, 0, kStorePolicy);
 }
 
+// Store v at byte `off` of the destination.
+__device__ __forceinline__ void store_stream_at(const StreamDst& d, uint32_t off, v4u v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, d.rsrc, off, 0, kStorePolicy);
+}
+
 }  // namespace kvx_dev

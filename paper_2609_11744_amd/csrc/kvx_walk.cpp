@@ -24,6 +24,10 @@ void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint3
   *shift = (*parts & (*parts - 1)) == 0 ? (uint32_t)__builtin_ctz(*parts) : 32u;
 }
 
+uint32_t copy_group(int layout, uint32_t n16) {
+  return layout != KVX_LAYOUT_PAGED_ATTN && n16 <= kGroupMaxVectors ? kPartThreads / n16 : 1;
+}
+
 namespace {
 
 // Whether a large scatter of small slabs walks the image in order with no
@@ -41,11 +45,21 @@ namespace {
 // head takes the linear walk too, with its heads on 256 threads
 // (kvx_kernels.hip): over 18 allocation pairs 73.2 % against 68.3 % for
 // destination order on 128 threads, and about 1 point with either change
-// alone; with two heads the linear walk lost 0.2 points.
+// alone; with two heads the linear walk lost 0.2 points. Slabs that neither
+// divide 4 KiB nor are whole multiples of it straddle the pieces that
+// consecutive workgroups of a linear walk write on different XCDs, so these
+// walk the image with XCD ranges. 1 GiB, 32 layers, linear / destination order
+// / image order with XCD ranges: 2,304 bytes 519 / 429 / 395 us, 2,560 bytes
+// 474 / 409 / 393, 3,840 bytes 409 / 387 / 395, 5,120 bytes 483 / 392 / 383,
+// 6 KiB 423 / 388 / 386, 7 KiB 398 / 388 / 386; 8 KiB 364 / 384 / 376. Grouped
+// ones the same: 1,920 bytes 414 / 407 / 399 us, 1,280 bytes 407 / 412 / 400.
+bool small_rows(int64_t slab, int layout, int32_t heads) {
+  return slab <= 8192 && (layout == KVX_LAYOUT_NHD || heads == 1);
+}
+
 bool scatter_linear(int64_t n_blocks, int64_t slab, int layout, int32_t heads) {
-  const bool rows = layout == KVX_LAYOUT_NHD ||
-                    ((layout == KVX_LAYOUT_HND || layout == KVX_LAYOUT_PAGED_ATTN) && heads == 1);
-  return rows && n_blocks >= kOrderedScatterMinBlocks && slab <= 8192;
+  return small_rows(slab, layout, heads) && n_blocks >= kOrderedScatterMinBlocks &&
+         (4096 % slab == 0 || slab % 4096 == 0);
 }
 
 // Whether a scatter of n_blocks in chunks of bpc blocks runs in destination
@@ -61,8 +75,7 @@ bool scatter_linear(int64_t n_blocks, int64_t slab, int layout, int32_t heads) {
 // 76.9 against 71.9 at 5,000 with 16).
 bool scatter_in_destination_order(int64_t n_blocks, int64_t bpc, int64_t slab, int layout,
                                   int32_t heads) {
-  return n_blocks >= kOrderedScatterMinBlocks && bpc > 1 &&
-         !scatter_linear(n_blocks, slab, layout, heads);
+  return n_blocks >= kOrderedScatterMinBlocks && bpc > 1 && !small_rows(slab, layout, heads);
 }
 
 // Pairing for the ordered scatter of n_work work items (one launch) over
@@ -132,12 +145,13 @@ kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g
   const uint32_t n16 = (uint32_t)(g.slab / 16), heads = (uint32_t)cache->num_kv_heads;
   w->pieces = slab_pieces(cache->layout, n16, heads);
   if ((uint64_t)g.n_units * w->pieces > 0x7FFFFFFF) return KVX_EINTERNAL;
-  copy_parts(copy_layout(cache->layout, cache->num_kv_heads, cache->block_size), n16, heads,
-             &w->parts, &w->parts_shift);
+  const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
+  copy_parts(layout, n16, heads, &w->parts, &w->parts_shift);
   const uint64_t n_work = (uint64_t)g.n_units * w->parts;
   // Pairs are chosen where both the pieces and the workgroups of a slab are a
-  // power of two.
-  const uint32_t pair_parts = w->pieces & (w->pieces - 1) ? 32u : w->parts_shift;
+  // power of two and slabs are not grouped.
+  const uint32_t pair_parts =
+      w->pieces & (w->pieces - 1) || copy_group(layout, n16) > 1 ? 32u : w->parts_shift;
   const uint32_t n_slices = (uint32_t)(2 * g.lr);
   if (to_packed) {
     w->gather_pair_shift = gather_pairing(pair_parts, n_slices, (uint32_t)g.bpc,
