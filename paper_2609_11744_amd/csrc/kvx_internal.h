@@ -50,19 +50,26 @@ constexpr int32_t kOrderedScatterMinBlocks = 1024;
 // the default layout, heads with the reordering ones).
 uint32_t slab_pieces(int layout, uint32_t n16, uint32_t heads);
 
-// The layout a cache is copied as: HND with one head or one token per block is
-// the default layout byte for byte.
+// The layout a cache is copied as: blocks of one token, and HND with one head,
+// are the default layout byte for byte.
 int copy_layout(int layout, int32_t heads, int32_t block_size);
 
-// Workgroups per slab for a copy_layout (4 KiB each with the default layout and
-// HND, a head each with paged attention), and log2 of that count when it is a
-// power of two (else 32: the kernels divide).
-void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift);
+// A paged-attention workgroup's tile of a slab: `heads` whole heads, or
+// `vectors` < v16 of every token's row of one head.
+struct TileShape {
+  uint32_t heads, vectors;
+};
+TileShape paged_tile(uint32_t block_size, uint32_t heads, uint32_t v16);
 
-// Slabs per workgroup for a copy_layout: 256 / n16 where at least two fit a
+// Workgroups per slab (4 KiB each with the default layout and HND, a tile each
+// with paged attention), and log2 of that count when it is a power of two
+// (else 32: the kernels divide).
+void copy_parts(const kvx_cache* cache, uint32_t n16, uint32_t* parts, uint32_t* shift);
+
+// Slabs per workgroup: 256 / n16 where at least two fit a
 // workgroup of one vector per thread, else 1.
 constexpr uint32_t kGroupMaxVectors = kPartThreads / 2;
-uint32_t copy_group(int layout, uint32_t n16);
+uint32_t copy_group(uint32_t n16);
 
 // How a gather or scatter walks its work items: the launcher's choice, also
 // reported by kvx_copy_walk (kvx_walk.cpp).

@@ -52,6 +52,7 @@
 // distances slower (scatter_pairing, gather_pairing in kvx_walk.cpp).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -106,6 +107,15 @@ struct SlabGeom {
   uint32_t x;      // elements per 16-byte vector: 16 / elem_bytes
   uint32_t nh;     // vectors of one head: bs * v16
   uint32_t prow;   // packed row stride in vectors: heads * v16
+  // Paged attention: a workgroup moves a tile of `gh` whole heads, or of `dw` of
+  // v16 vectors of every token's row of one head (paged_tile).
+  uint32_t heads;
+  uint32_t gh;
+  uint32_t dw;
+  FastDiv dpieces;   // v16 / dw
+  FastDiv row;       // gh * dw: vectors of a token in the tile
+  FastDiv np;        // bs * dw: vectors of a head in the tile
+  FastDiv dwd;       // dw
   // HND: destination vector w of a slab is (w / outer, rest / v16, rest % v16)
   // = (a, b, dv) and comes from source vector a * v16 + b * src_step + dv
   // (gather: a token, b head; scatter: a head, b token).
@@ -116,7 +126,10 @@ struct SlabGeom {
 
   FastDiv pad;       // scatter: LDS pad period (see lds_slot)
   uint32_t v_pairs;  // paged-attention V of 2-byte words gathered as row pairs (v_pairs_gather)
+  uint32_t v_bytes;  // paged-attention V of 1-byte words by transpose reads (v_bytes)
+  FastDiv bs16;      // bs / 16, where v_bytes
   uint32_t swz;      // gather: LDS swizzle shift (see lds_slot)
+  uint32_t image;    // vectors of a tile's LDS image: whole swizzle groups of 16, or with pads
 };
 
 // Division of any 32-bit numerator by a divisor fixed for the launch, as a
@@ -228,27 +241,39 @@ __device__ __forceinline__ void move_piece(const v4u* __restrict__ s, v4u* __res
 //                          [head][dim][token] (an element transpose).
 // In every one of them a head's data is contiguous on the cache side (nh =
 // bs * v16 vectors), and on the packed side it is one v16-vector row per token
-// at stride prow = heads * v16. So a workgroup moves one head (the slab's
-// parts are its heads), one vector per thread for the usual shapes; inside a
-// head, local packed vector w = t * v16 + dv sits at packed_at(w).
-//   * HND: the head's cache rows are its packed rows in the same order, so
-//     vectors move directly (no LDS); the packed side is 16 * v16-byte runs.
-//   * paged-attention K: a vector permutation. The head is loaded in source
+// at stride prow = heads * v16.
+//   * HND: vectors move directly (no LDS). A workgroup writes 256 consecutive
+//     vectors of the destination slab and reads runs of v16 vectors (or the
+//     parts of them that its piece covers).
+//   * paged attention: a workgroup moves a tile of about 256 vectors: whole
+//     neighbouring heads where they are small, and where a head is larger a
+//     run of at least 128 bytes of each of its tokens' rows (tile_geom). Either
+//     way the tile is contiguous on the cache side and a run per token on the
+//     packed side.
+//   * paged-attention K: a vector permutation. The tile is loaded in source
 //     order into LDS, then written in destination order, each lane fetching
 //     the source vector its output vector is. (Moving each vector straight
 //     from its source to its destination, the packed side then in 64-byte
 //     runs, measured 2.3 points slower both ways on the 80k workload: the
 //     wave-contiguous runs on both sides are worth more than the LDS pass.)
-//   * paged-attention V: an element transpose. The head is loaded in source
+//   * paged-attention V: an element transpose. The tile is loaded in source
 //     order into LDS, then each output vector is assembled element by element
 //     from it.
 // Both global sides stay coalesced (consecutive lanes on consecutive 16-byte
-// vectors, or whole packed rows) and only LDS sees the reordering; the LDS
-// image is swizzled so that a wave's strided reads land on distinct banks. A
-// thread holds V vectors of the head, all of its loads issued before it waits
-// for any of them: V = 1 when a head fits one vector per thread (the usual
-// shapes: few registers, full occupancy), else kVecPerThread, enough for the
-// largest head (kMaxSlabVectors).
+// vectors, or whole runs) and only LDS sees the reordering; the LDS image is
+// swizzled so that a wave's strided reads land on distinct banks. A thread
+// holds V vectors of the tile, all of its loads issued before it waits for any
+// of them: V = 1 for tiles of up to 256 vectors (the usual shapes: few
+// registers, full occupancy), 2 or 4 for blocks of many tokens, else
+// kVecPerThread, enough for the largest head (kMaxSlabVectors).
+// Against one head per workgroup, with 12 vectors a thread for heads above 256
+// vectors (1 GiB, 32 layers, gather / scatter, before -> now):
+//   16-token blocks, 8 x 128 bf16    341 / 390 -> 342 / 391 us
+//   8 x 128 8-bit                    534 / 412 -> 353 / 385 us
+//   4 x 64 8-bit                     906 / 608 -> 353 / 397 us
+//   32-token blocks, 4 x 128 bf16    464 / 374 -> 345 / 374 us
+//   64-token blocks, 2 x 128 bf16    361 / 387 -> 356 / 379 us
+//   5 x 80 bf16                      564 / 411 -> 409 / 395 us
 
 constexpr int kTransposeThreads = 256;
 constexpr uint32_t kMaxSlabVectors = 48 * 1024 / 16;
@@ -275,10 +300,14 @@ extern __shared__ __attribute__((aligned(16))) unsigned char kvx_lds[];
 // with it (also with no conflicts left): it is not bound by the LDS, and the
 // swizzle's extra arithmetic in its element-by-element loop costs more than
 // the conflicts it removes.
-template <bool kToPacked>
+// 1-byte words take another h, r rotated by one bit: the transposing reads of a
+// half-wave (v_bytes) cover 8 consecutive vectors of rows r and r + 1, which
+// bit 0 of r then keeps in different halves of the group.
+template <bool kToPacked, int kElem>
 __device__ __forceinline__ uint32_t lds_slot(uint32_t v, const SlabGeom& g) {
   if (kToPacked) {
     const uint32_t r = (v >> g.swz) & 15u;
+    if (kElem == 1) return v ^ (((r & 1u) << 3) | (r >> 1));
     return v ^ (r ^ ((r >> 2) & 2u));
   }
   return v + fdiv(v, g.pad);
@@ -289,21 +318,6 @@ __device__ __forceinline__ uint32_t divmod(uint32_t n, FastDiv f, uint32_t& rem)
   const uint32_t q = fdiv(n, f);
   rem = n - q * f.d;
   return q;
-}
-
-// Bytes a head's moves write from the destination's first vector: the head's
-// packed rows (a gather) or its nh contiguous cache vectors (a scatter).
-template <bool kToPacked>
-__device__ __forceinline__ uint32_t head_dst_bytes(const SlabGeom& g) {
-  return (kToPacked ? (g.bs.d - 1) * g.prow + g.v16.d : g.nh) * 16u;
-}
-
-// Packed-side offset (in vectors, from the head's first row) of local packed
-// vector w = t * v16 + dv.
-__device__ __forceinline__ uint32_t packed_at(uint32_t w, const SlabGeom& g) {
-  uint32_t dv;
-  const uint32_t t = divmod(w, g.v16, dv);
-  return t * g.prow + dv;
 }
 
 // HND: source vector of destination vector w of a slab.
@@ -324,22 +338,60 @@ __device__ __forceinline__ void move_rows(const v4u* __restrict__ src, v4u* __re
   if (w < (end < n16 ? end : n16)) store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
 }
 
-// Load the head's nh source vectors, in source order, into the padded LDS
-// image. A gather reads the cache (contiguous), a scatter the packed rows.
-template <bool kToPacked, int T, int V>
-__device__ __forceinline__ void stage_in(const v4u* __restrict__ src, const SlabGeom& g) {
+// A workgroup's tile of a paged-attention slab: its first vector on the cache
+// side (contiguous from there) and on the packed side (a run of row.d vectors
+// per token), and the vectors it has (the last tile of a slab may hold fewer
+// heads than gh: the rest of its lanes idle).
+struct Tile {
+  uint32_t cache0, packed0;
+  uint32_t heads;
+};
+
+__device__ __forceinline__ Tile tile_at(uint32_t part, const SlabGeom& g) {
+  if (g.gh == 1 && g.dpieces.d == 1) return Tile{part * g.nh, part * g.v16.d, 1};
+  uint32_t piece;
+  const uint32_t group = divmod(part, g.dpieces, piece), h0 = group * g.gh;
+  const uint32_t left = g.heads - h0;
+  return Tile{h0 * g.nh + piece * g.np.d, h0 * g.v16.d + piece * g.dw, left < g.gh ? left : g.gh};
+}
+
+// Vector w of the tile in packed order (token by token, then head, then
+// vector): its packed-side offset from the tile's first vector; ok = false for
+// a head the slab does not have.
+__device__ __forceinline__ uint32_t packed_at(uint32_t w, const SlabGeom& g, const Tile& tile,
+                                              bool* ok) {
+  uint32_t q;
+  const uint32_t t = divmod(w, g.row, q);
+  *ok = t < g.bs.d && q < tile.heads * g.dw;
+  return t * g.prow + q;
+}
+
+// The same offset in the direction's destination or source order: the cache
+// side is contiguous.
+template <bool kPackedSide>
+__device__ __forceinline__ uint32_t side_at(uint32_t w, const SlabGeom& g, const Tile& tile,
+                                            bool* ok) {
+  if (kPackedSide) return packed_at(w, g, tile, ok);
+  *ok = w < tile.heads * g.np.d;
+  return w;
+}
+
+// Load the tile's source vectors, in source order, into the LDS image. A gather
+// reads the cache (contiguous), a scatter the packed rows.
+template <bool kToPacked, int kElem, int T, int V>
+__device__ __forceinline__ void stage_in(const v4u* __restrict__ src, const SlabGeom& g,
+                                         const Tile& tile) {
   v4u* lds = reinterpret_cast<v4u*>(kvx_lds);
   v4u r[V];
+  bool ok[V];
 #pragma unroll
   for (int q = 0; q < V; ++q) {
-    const uint32_t v = threadIdx.x + q * T;
-    if (v < g.nh) r[q] = __builtin_nontemporal_load(src + (kToPacked ? v : packed_at(v, g)));
+    const uint32_t at = side_at<!kToPacked>(threadIdx.x + q * T, g, tile, &ok[q]);
+    if (ok[q]) r[q] = __builtin_nontemporal_load(src + at);
   }
 #pragma unroll
-  for (int q = 0; q < V; ++q) {
-    const uint32_t v = threadIdx.x + q * T;
-    if (v < g.nh) lds[lds_slot<kToPacked>(v, g)] = r[q];
-  }
+  for (int q = 0; q < V; ++q)
+    if (ok[q]) lds[lds_slot<kToPacked, kElem>(threadIdx.x + q * T, g)] = r[q];
 }
 
 // The LDS serves 32-bit and narrower reads a half-wave (32 lanes) at a time
@@ -357,35 +409,57 @@ __device__ __forceinline__ uint32_t lane_perm(uint32_t i) {
   return (i & ~63u) | (((l >> 3) & 3u) << 4) | (((l >> 5) & 1u) << 3) | (l & 7u);
 }
 
-// Write the head's nh destination vectors, in destination order, each
-// produced by f(w). A gather writes the packed rows, a scatter the cache.
+// Bytes a tile's stores may reach from its first destination vector.
+template <bool kToPacked>
+__device__ __forceinline__ uint32_t tile_dst_bytes(const SlabGeom& g) {
+  return (kToPacked ? (g.bs.d - 1) * g.prow + g.row.d : g.gh * g.np.d) * 16u;
+}
+
+// Write the tile's destination vectors, in destination order, each produced by
+// f(w). A gather writes the packed rows, a scatter the cache.
 template <bool kToPacked, int T, int V, typename F>
-__device__ __forceinline__ void stage_out(v4u* __restrict__ dst, const SlabGeom& g, F f) {
+__device__ __forceinline__ void stage_out(v4u* __restrict__ dst, const SlabGeom& g,
+                                          const Tile& tile, F f) {
   v4u r[V];
+  uint32_t at[V];
+  bool ok[V];
 #pragma unroll
   for (int q = 0; q < V; ++q) {
-    const uint32_t w = threadIdx.x + q * T;
-    if (w < g.nh) r[q] = f(w);
+    at[q] = side_at<kToPacked>(threadIdx.x + q * T, g, tile, &ok[q]);
+    if (ok[q]) r[q] = f(threadIdx.x + q * T);
   }
-  const auto out = stream_dst(dst, head_dst_bytes<kToPacked>(g));
+  const auto out = stream_dst(dst, tile_dst_bytes<kToPacked>(g));
 #pragma unroll
-  for (int q = 0; q < V; ++q) {
-    const uint32_t w = threadIdx.x + q * T;
-    if (w < g.nh) store_stream(out, kToPacked ? packed_at(w, g) : w, r[q]);
-  }
+  for (int q = 0; q < V; ++q)
+    if (ok[q]) store_stream(out, at[q], r[q]);
+}
+
+// Head and rest of a tile's vector: index in packed order -> (token, head of the
+// tile, vector of the head's row); in cache order -> (head, vector of the head).
+__device__ __forceinline__ void packed_split(uint32_t w, const SlabGeom& g, uint32_t* t,
+                                             uint32_t* h, uint32_t* dv) {
+  *t = divmod(w, g.row, *dv);
+  *h = 0;
+  if (g.gh > 1) *h = divmod(*dv, g.dwd, *dv);
+}
+
+__device__ __forceinline__ uint32_t cache_split(uint32_t w, const SlabGeom& g, uint32_t* r) {
+  *r = w;
+  return g.gh > 1 ? divmod(w, g.np, *r) : 0;
 }
 
 // Paged-attention K: source vector (in the LDS image) of destination vector w.
-// Cache order inside a head is w = dv * bs + t, packed order w = t * v16 + dv.
+// Cache order inside a head is dv * bs + t, packed order (t, head, dv).
 template <bool kToPacked>
 __device__ __forceinline__ uint32_t k_source(uint32_t w, const SlabGeom& g) {
-  uint32_t lo;
+  uint32_t t, h, dv, r;
   if (kToPacked) {
-    const uint32_t t = divmod(w, g.v16, lo);  // lo = dv
-    return lo * g.bs.d + t;
+    packed_split(w, g, &t, &h, &dv);
+    return h * g.np.d + dv * g.bs.d + t;
   }
-  const uint32_t dv = divmod(w, g.bs, lo);    // lo = t
-  return lo * g.v16.d + dv;
+  h = cache_split(w, g, &r);
+  dv = divmod(r, g.bs, t);
+  return t * g.row.d + h * g.dw + dv;
 }
 
 template <typename E>
@@ -395,27 +469,31 @@ struct ElemRow {
 
 // Paged-attention V: destination vector w assembled element by element from
 // the LDS image of the source. Cache elements inside a head are (dim, t) at
-// dim * bs + t; packed elements (t, dim) at t * d + dim.
+// dim * bs + t; packed elements (t, head, dim).
 template <bool kToPacked, typename E>
-__device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g) {
+__device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g,
+                                          const unsigned char* image) {
   constexpr uint32_t kX = 16 / sizeof(E);
   ElemRow<E> out;
   if (kToPacked) {  // packed (t, dv * x + i) <- cache element (dv * x + i, t): stride bs
-    uint32_t dv;
-    const uint32_t t = divmod(w, g.v16, dv);
-    const uint32_t e0 = dv * kX * g.bs.d + t;
+    uint32_t t, h, dv;
+    packed_split(w, g, &t, &h, &dv);
+    const uint32_t e0 = (h * g.np.d + dv * g.bs.d) * kX + t;
 #pragma unroll
     for (uint32_t i = 0; i < kX; ++i) {
       const uint32_t e = e0 + i * g.bs.d;
-      out.e[i] = reinterpret_cast<const E*>(kvx_lds + 16u * lds_slot<kToPacked>(e / kX, g))[e % kX];
+      out.e[i] = reinterpret_cast<const E*>(
+          image + 16u * lds_slot<kToPacked, sizeof(E)>(e / kX, g))[e % kX];
     }
   } else {  // cache (dim, t .. t + x - 1) <- packed elements (t + i, dim); t wraps to dim + 1
-    uint32_t t;
-    uint32_t dim = divmod(w * kX, g.bs, t);
+    uint32_t r, t;
+    const uint32_t h = cache_split(w, g, &r);
+    uint32_t dim = h * g.dw * kX + divmod(r * kX, g.bs, t);
 #pragma unroll
     for (uint32_t i = 0; i < kX; ++i) {
-      const uint32_t e = t * g.d.d + dim;
-      out.e[i] = reinterpret_cast<const E*>(kvx_lds + 16u * lds_slot<kToPacked>(e / kX, g))[e % kX];
+      const uint32_t e = t * (g.row.d * kX) + dim;
+      out.e[i] = reinterpret_cast<const E*>(
+          image + 16u * lds_slot<kToPacked, sizeof(E)>(e / kX, g))[e % kX];
       if (++t == g.bs.d) {
         t = 0;
         ++dim;
@@ -434,66 +512,137 @@ __device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g) {
 // stores of a lane write whole token rows. A scatter does not pair its
 // vectors this way: paired dims d, d + 1 would make each store instruction
 // write every other 32-byte run of the cache lines (the 80k scatter ran at
-// half speed that way).
+// half speed that way). Pairs take half of a tile's threads, so a thread has
+// (V + 1) / 2 of them.
 template <int T, int V>
-__device__ __forceinline__ void v_pairs_gather(v4u* __restrict__ dst, const SlabGeom& g) {
+__device__ __forceinline__ void v_pairs_gather(v4u* __restrict__ dst, const SlabGeom& g,
+                                               const Tile& tile) {
   typedef ElemRow<uint16_t> Row;
-  const uint32_t np = g.nh >> 1;
-  Row r0[V], r1[V];
-  uint32_t w0[V];
+  constexpr int P = (V + 1) / 2;
+  Row r0[P], r1[P];
+  uint32_t at[P];
+  bool ok[P];
 #pragma unroll
-  for (int q = 0; q < V; ++q) {
+  for (int q = 0; q < P; ++q) {
     // a half-wave takes 4 token pairs x 8 dim groups (16 vectors per row)
     const uint32_t p = lane_perm(threadIdx.x + q * T);
-    if (p >= np) continue;
-    uint32_t dv;
-    const uint32_t tp = divmod(p, g.v16, dv);  // tokens 2 tp, 2 tp + 1
-    w0[q] = 2 * tp * g.v16.d + dv;
-    const uint32_t e0 = dv * 8 * g.bs.d + 2 * tp;
+    uint32_t tp, h, dv;
+    packed_split(p, g, &tp, &h, &dv);  // tokens 2 tp, 2 tp + 1
+    ok[q] = 2 * tp < g.bs.d && h < tile.heads;
+    if (!ok[q]) continue;
+    at[q] = 2 * tp * g.prow + h * g.dw + dv;
+    const uint32_t e0 = (h * g.np.d + dv * g.bs.d) * 8 + 2 * tp;
 #pragma unroll
     for (uint32_t i = 0; i < 8; ++i) {
       const uint32_t e = e0 + i * g.bs.d;
-      const uint32_t w = *reinterpret_cast<const uint32_t*>(kvx_lds + 16u * lds_slot<true>(e >> 3, g) +
-                                                            2u * (e & 7u));
+      const uint32_t w = *reinterpret_cast<const uint32_t*>(
+          kvx_lds + 16u * lds_slot<true, 2>(e >> 3, g) + 2u * (e & 7u));
       r0[q].e[i] = (uint16_t)w;
       r1[q].e[i] = (uint16_t)(w >> 16);
     }
   }
-  const auto out = stream_dst(dst, head_dst_bytes<true>(g));
+  const auto out = stream_dst(dst, tile_dst_bytes<true>(g));
 #pragma unroll
-  for (int q = 0; q < V; ++q) {
-    const uint32_t p = lane_perm(threadIdx.x + q * T);
-    if (p >= np) continue;
-    store_stream(out, packed_at(w0[q], g), __builtin_bit_cast(v4u, r0[q]));
-    store_stream(out, packed_at(w0[q] + g.v16.d, g), __builtin_bit_cast(v4u, r1[q]));
+  for (int q = 0; q < P; ++q) {
+    if (!ok[q]) continue;
+    store_stream(out, at[q], __builtin_bit_cast(v4u, r0[q]));
+    store_stream(out, at[q] + g.prow, __builtin_bit_cast(v4u, r1[q]));
   }
 }
 
-// One head of a slab in a reordering layout (src / dst: the head's cache
-// vectors and its first packed row, in the kernel's direction).
-template <bool kToPacked, int kLayout, int kElem, int T, int V>
-__device__ __forceinline__ void move_head(const v4u* __restrict__ src, v4u* __restrict__ dst,
-                                          const SlabGeom& g, uint32_t kv) {
+// Paged-attention V of 1-byte words in blocks of a multiple of 16 tokens, with
+// the LDS transpose reads of gfx950: ds_read_b64_tr_b8 over 16 lanes, lane l
+// giving the address of bytes 8 (l % 2) .. + 7 of row l / 2 of an 8 x 16 byte
+// matrix, returns its column l to lane l. Two of them make one destination
+// vector per lane, 16 rows of one column, where the element loop above takes
+// sixteen byte reads. A gather transposes 16 dims x 16 tokens (rows: dims),
+// a scatter 16 tokens x 16 dims. Vector w of the tile, in the order in which
+// lanes take them: 16-lane group k = w / 16 of (head, 16 tokens, 16 dims); at:
+// its destination offset. 8 x 128 dims, 16 tokens, 1 GiB: gather 365 -> 353 us,
+// scatter 400 -> 385 us against element by element.
+typedef int v2i __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
+  return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
+      (__attribute__((address_space(3))) v2i*)const_cast<unsigned char*>(p));
+}
+
+template <bool kToPacked>
+__device__ __forceinline__ v4u v_bytes(uint32_t w, const SlabGeom& g, const unsigned char* image,
+                                       uint32_t* at) {
+  const uint32_t k = w >> 4, l = w & 15u;
+  uint32_t tg, dv, h, first, step;
+  if (kToPacked) {  // rows: dims 16 dv + i; columns: tokens 16 tg ..
+    h = divmod(divmod(k, g.dwd, dv), g.bs16, tg);
+    first = h * g.np.d + dv * g.bs.d + (l >> 1) * g.bs16.d + tg;
+    step = 8 * g.bs16.d;
+    *at = (16 * tg + l) * g.prow + h * g.dw + dv;
+  } else {  // rows: tokens 16 tg + i; columns: dims 16 dv ..
+    h = divmod(divmod(k, g.bs16, tg), g.dwd, dv);
+    first = (16 * tg + (l >> 1)) * g.row.d + h * g.dw + dv;
+    step = 8 * g.row.d;
+    *at = h * g.np.d + (16 * dv + l) * g.bs16.d + tg;
+  }
+  // Odd groups read their rows 8 .. 15 first: a scatter's rows lie a vector
+  // apart modulo the banks, and neighbouring groups' would meet there.
+  const bool odd = !kToPacked && (k & 1u);
+  const uint32_t a = odd ? first + step : first, b = odd ? first : first + step;
+  const unsigned char* half = image + 8u * (l & 1u);
+  const v2i x = read_tr8(half + 16u * lds_slot<kToPacked, 1>(a, g));
+  const v2i y = read_tr8(half + 16u * lds_slot<kToPacked, 1>(b, g));
+  const v2i lo = odd ? y : x, hi = odd ? x : y;
+  return v4u{(uint32_t)lo.x, (uint32_t)lo.y, (uint32_t)hi.x, (uint32_t)hi.y};
+}
+
+template <bool kToPacked, int T, int V>
+__device__ __forceinline__ void v_bytes_out(v4u* __restrict__ dst, const SlabGeom& g,
+                                            const Tile& tile) {
+  v4u r[V];
+  uint32_t at[V];
+  bool ok[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    const uint32_t w = threadIdx.x + q * T;
+    ok[q] = w < tile.heads * g.np.d;  // the same for the 16 lanes of a group
+    if (ok[q]) r[q] = v_bytes<kToPacked>(w, g, kvx_lds, &at[q]);
+  }
+  const auto out = stream_dst(dst, tile_dst_bytes<kToPacked>(g));
+#pragma unroll
+  for (int q = 0; q < V; ++q)
+    if (ok[q]) store_stream(out, at[q], r[q]);
+}
+
+// One tile of a paged-attention slab (pv, pk: the slab's first vector on the
+// cache and on the packed side).
+template <bool kToPacked, int kElem, int T, int V>
+__device__ __forceinline__ void move_tile(v4u* pv, v4u* pk, const SlabGeom& g, uint32_t kv,
+                                          uint32_t part) {
   typedef typename std::conditional<
       kElem == 1, uint8_t,
       typename std::conditional<kElem == 2, uint16_t,
                                 typename std::conditional<kElem == 4, uint32_t,
                                                           uint64_t>::type>::type>::type E;
-  stage_in<kToPacked, T, V>(src, g);
+  const Tile tile = tile_at(part, g);
+  const v4u* src = kToPacked ? pv + tile.cache0 : pk + tile.packed0;
+  v4u* dst = kToPacked ? pk + tile.packed0 : pv + tile.cache0;
+  stage_in<kToPacked, kElem, T, V>(src, g, tile);
   __syncthreads();
   const v4u* lds = reinterpret_cast<const v4u*>(kvx_lds);
   if (kv == 0)
-    stage_out<kToPacked, T, V>(
-        dst, g, [&](uint32_t w) { return lds[lds_slot<kToPacked>(k_source<kToPacked>(w, g), g)]; });
+    stage_out<kToPacked, T, V>(dst, g, tile, [&](uint32_t w) {
+      return lds[lds_slot<kToPacked, kElem>(k_source<kToPacked>(w, g), g)];
+    });
+  else if (kElem == 1 && g.v_bytes)
+    v_bytes_out<kToPacked, T, V>(dst, g, tile);
   else if (kToPacked && kElem == 2 && g.v_pairs)
-    v_pairs_gather<T, V>(dst, g);
+    v_pairs_gather<T, V>(dst, g, tile);
   else
-    stage_out<kToPacked, T, V>(dst, g,
-                               [&](uint32_t w) { return v_elements<kToPacked, E>(w, g); });
+    stage_out<kToPacked, T, V>(
+        dst, g, tile, [&](uint32_t w) { return v_elements<kToPacked, E>(w, g, kvx_lds); });
 }
 
 // Move part `part` of one slab in the direction and layout of the kernel: a
-// 4 KiB piece with the default layout and HND, one head with paged attention.
+// 4 KiB piece with the default layout and HND, one tile with paged attention.
 template <bool kToPacked, int kLayout, int kElem, int T, int V>
 __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, const SlabGeom& g,
                                           uint32_t kv, uint32_t part) {
@@ -513,12 +662,7 @@ __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, c
     else
       move_rows(kv4, pv, n16, g, part);
   } else {
-    v4u* cache_head = pv + part * g.nh;       // head `part`: nh contiguous cache vectors
-    v4u* packed_head = kv4 + part * g.v16.d;  // its first packed row
-    if (kToPacked)
-      move_head<true, kLayout, kElem, T, V>(cache_head, packed_head, g, kv);
-    else
-      move_head<false, kLayout, kElem, T, V>(packed_head, cache_head, g, kv);
+    move_tile<kToPacked, kElem, T, V>(pv, kv4, g, kv, part);
   }
 }
 
@@ -695,6 +839,7 @@ struct Place {
   char* paged;
   char* packed;
   char* base;  // at or below this lane's destination, the same or nearby for the wave's lanes
+  uint32_t kv;
   bool ok;
 };
 
@@ -738,6 +883,33 @@ __device__ __forceinline__ void move_grouped(const Place& p, uint32_t w, const S
   store_grouped<kWave>(p.base, dst, g.n16.d, w, __builtin_nontemporal_load(src + from));
 }
 
+// Paged attention: each slab of the group has an LDS image of its own and is one
+// tile (gh = heads, dw = v16). Called by every thread of the workgroup.
+template <bool kToPacked, int kElem>
+__device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, uint32_t w,
+                                                   const SlabGeom& g) {
+  typedef typename std::conditional<
+      kElem == 1, uint8_t,
+      typename std::conditional<kElem == 2, uint16_t,
+                                typename std::conditional<kElem == 4, uint32_t,
+                                                          uint64_t>::type>::type>::type E;
+  unsigned char* image = kvx_lds + 16u * (i * g.image);
+  v4u* lds = reinterpret_cast<v4u*>(image);
+  if (p.ok)
+    lds[lds_slot<kToPacked, kElem>(w, g)] = __builtin_nontemporal_load(
+        reinterpret_cast<const v4u*>(kToPacked ? p.paged : p.packed) + w);
+  __syncthreads();
+  if (!p.ok) return;
+  v4u v;
+  if (p.kv == 0)
+    v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked>(w, g), g)];
+  else if (kElem == 1 && g.v_bytes)
+    v = v_bytes<kToPacked>(w, g, image, &w);
+  else
+    v = v_elements<kToPacked, E>(w, g, image);
+  store_grouped<false>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
+}
+
 // Unit u of a grouped call in image order, or (kOrdered) slice by slice in the
 // order's ascending destinations.
 template <bool kToPacked, bool kOrdered>
@@ -767,10 +939,12 @@ __device__ __forceinline__ Place place_unit(const LayerPtrs& layers, const int32
   p.paged = layer + (uint64_t)(uint32_t)id * g.slab;
   p.packed = packed + (uint64_t)u * g.slab;
   p.base = kToPacked ? p.packed : layer;
+  p.kv = lk & 1;
   return p;
 }
 
-template <bool kToPacked, bool kOrdered, int kLayout, bool kWave>
+// kElem: the word size with paged attention, else 0.
+template <bool kToPacked, bool kOrdered, int kLayout, int kElem, bool kWave>
 __global__ void __launch_bounds__(kPartThreads)
     copy_unit_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table, UnitGeom g,
                             uint32_t group_base, uint32_t group_count,
@@ -781,10 +955,13 @@ __global__ void __launch_bounds__(kPartThreads)
   const uint32_t u = (group_base + (g.linear_walk ? blockIdx.x
                                                   : xcd_contiguous(blockIdx.x, group_count))) *
                          g.group + i;
-  if (i >= g.group || u >= g.n_units) return;
-  const Place p = place_unit<kToPacked, kOrdered>(layers, block_table, g, u, order, packed, err,
-                                                  w == 0);
-  if (p.ok) move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
+  Place p = {};
+  if (i < g.group && u < g.n_units)
+    p = place_unit<kToPacked, kOrdered>(layers, block_table, g, u, order, packed, err, w == 0);
+  if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN)
+    move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+  else if (p.ok)
+    move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
 
 // Unit u of a chunk list's padded unit space (copy_chunks_kernel).
@@ -811,10 +988,11 @@ __device__ __forceinline__ Place place_chunk_unit(const LayerPtrs& layers,
   p.paged = layer + (uint64_t)(uint32_t)id * g.slab;
   p.packed = packed + ref.packed_offset + (uint64_t)(lk * nc + j) * g.slab;
   p.base = kToPacked ? packed : layer;
+  p.kv = lk & 1;
   return p;
 }
 
-template <bool kToPacked, int kLayout, bool kWave>
+template <bool kToPacked, int kLayout, int kElem, bool kWave>
 __global__ void __launch_bounds__(kPartThreads)
     copy_chunk_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
                              const kvx_chunk_ref* __restrict__ refs, ChunkGeom g,
@@ -823,9 +1001,13 @@ __global__ void __launch_bounds__(kPartThreads)
   uint32_t w;
   const uint32_t i = grouped_unit<kWave>(g.sg, &w);
   const uint32_t u = (group_base + xcd_contiguous(blockIdx.x, group_count)) * g.group + i;
-  if (i >= g.group || u >= g.n_units) return;
-  const Place p = place_chunk_unit<kToPacked>(layers, block_table, refs, g, u, packed, err, w == 0);
-  if (p.ok) move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
+  Place p = {};
+  if (i < g.group && u < g.n_units)
+    p = place_chunk_unit<kToPacked>(layers, block_table, refs, g, u, packed, err, w == 0);
+  if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN)
+    move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+  else if (p.ok)
+    move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
 
 // Destination order for a scatter: order[] lists the block-table indexes,
@@ -887,57 +1069,66 @@ __global__ void __launch_bounds__(kOrderThreads)
   }
 }
 
-// Dynamic LDS bytes for a reordering layout: the image of one head, rounded
-// up to whole swizzle groups of 16 vectors (gather) or with its pad vectors
-// (scatter); none for HND, which moves rows directly.
-inline size_t lds_bytes(int layout, const SlabGeom& sg, bool to_packed) {
-  if (layout != KVX_LAYOUT_PAGED_ATTN) return 0;
-  if (to_packed) return 16u * (size_t)((sg.nh + 15u) & ~15u);
-  return 16u * (size_t)(sg.nh + sg.nh / sg.pad.d + 1);
-}
-
-// Launch `cnt` workgroups of kernel K<..., layout, elem, T, V>: the default
-// layout moves 4 KiB parts (kPartThreads threads x 1 vector); the others move
-// one head per workgroup of 256 threads (paged attention through LDS).
 #define KVX_UNPAREN(...) __VA_ARGS__
 
-// Whether a paged-attention scatter of heads that fit one vector per thread
-// runs them on half as many threads with two vectors each. Twice as many of
+// Whether a paged-attention scatter of tiles of at most 256 vectors runs them
+// on half as many threads with two vectors each. Twice as many of
 // its workgroups then fit a compute unit, which keeps more loads in flight
 // across its LDS phases. Measured over 12-18 (cache, packed buffer)
 // allocation pairs in one process at the 80k prefix of the 8B shape, against
 // one vector on each of 256 threads: 81.2 against 78.9 % of peak with 8
 // heads, level with 4 (75.3 / 75.2 %), 69.4 against 69.9 % with 2 and, with
 // the linear walk a one-head scatter takes (kvx_walk.cpp), 69.6 against
-// 73.2 % with 1. So only slabs of four heads or more take it.
+// 73.2 % with 1. So only slabs of four heads or more take it, and not tiles
+// that are pieces of a head (4 heads of 32 tokens x 128 dims: 390 us on half the
+// threads, 374 on 256, 1 GiB).
 inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
-  return sg.nh <= (uint32_t)kTransposeThreads && sg.prow >= 4u * sg.v16.d;
+  return sg.gh * sg.np.d <= (uint32_t)kTransposeThreads && sg.heads >= 4 && sg.dpieces.d == 1;
 }
 
-// One head per workgroup of kTransposeThreads: one vector per thread when the
-// head fits, else kVecPerThread; a paged-attention scatter of four or more
-// such heads per slab on half the threads (pa_scatter_on_half_threads; the
-// gather and the HND layout were no faster that way). PREFIX is the kernel's
-// parenthesized leading template arguments; kToPacked is the enclosing
-// launcher's direction.
-#define KVX_LAUNCH_HEADS(KERNEL, PREFIX, LAYOUT, ELEM, ...)                                 \
+// Dynamic LDS bytes of a workgroup of T threads with V vectors each: the tile's
+// image. Tiles that fill two or more vectors a thread reserve enough that six
+// workgroups run on a compute unit: eight would keep 64 KiB or more of reads in
+// flight there. 1 GiB, 32 layers, gather / scatter, 64-token blocks of 128
+// dims: 2 heads bf16 375 / 394 us unheld, 360 / 382 held; 2 heads 8-bit 376 /
+// 402 and 365 / 387; 4 heads 8-bit 382 / 389 and 355 / 375 (held to four 373 /
+// 384). Tiles with idle lanes lost up to 10 % held (5 x 96 dims 8-bit: 375 / 394
+// and 413 / 399).
+inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
+  constexpr size_t kSixPerUnit = 27000;
+  const size_t image = 16u * (size_t)sg.image;
+  return V > 1 && T == (uint32_t)kTransposeThreads && sg.gh * sg.np.d == T * V
+             ? std::max(image, kSixPerUnit)
+             : image;
+}
+
+// Launch a paged-attention kernel: a tile per workgroup of kTransposeThreads
+// with 1, 2, 4 or kVecPerThread vectors a thread, a scatter of four or more
+// heads per slab on half the threads (pa_scatter_on_half_threads; the gather
+// was no faster that way). PREFIX is the kernel's parenthesized leading
+// template arguments; kToPacked is the enclosing launcher's direction.
+#define KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, V, ...)                                    \
+  hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, T, V>), grid, \
+                     dim3(T), tile_lds(sg, T, V), stream, __VA_ARGS__)
+
+#define KVX_LAUNCH_TILES(KERNEL, PREFIX, ELEM, ...)                                         \
   do {                                                                                 \
-    const dim3 tb(kTransposeThreads);                                                  \
-    if constexpr (LAYOUT == KVX_LAYOUT_PAGED_ATTN && !kToPacked) {                     \
+    const uint32_t n = sg.gh * sg.np.d;                                                \
+    constexpr int T = kTransposeThreads;                                               \
+    if constexpr (!kToPacked) {                                                        \
       if (pa_scatter_on_half_threads(sg)) {                                            \
-        hipLaunchKernelGGL(                                                            \
-            (KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, kTransposeThreads / 2, 2>), grid, \
-            dim3(kTransposeThreads / 2), lds_bytes(layout, sg, kToPacked), stream, __VA_ARGS__);  \
+        KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T / 2, 2, __VA_ARGS__);                  \
         break;                                                                         \
       }                                                                                \
     }                                                                                  \
-    if (sg.nh <= (uint32_t)kTransposeThreads)                                          \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, kTransposeThreads, 1>), \
-                         grid, tb, lds_bytes(layout, sg, kToPacked), stream, __VA_ARGS__);        \
+    if (n <= (uint32_t)T)                                                              \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 1, __VA_ARGS__);                        \
+    else if (n <= 2u * T)                                                              \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 2, __VA_ARGS__);                        \
+    else if (n <= 4u * T)                                                              \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 4, __VA_ARGS__);                        \
     else                                                                               \
-      hipLaunchKernelGGL(                                                              \
-          (KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, kTransposeThreads, kVecPerThread>), \
-          grid, tb, lds_bytes(layout, sg, kToPacked), stream, __VA_ARGS__);                       \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, kVecPerThread, __VA_ARGS__);            \
   } while (0)
 
 #define KVX_DISPATCH(KERNEL, PREFIX, ...)                                                   \
@@ -950,13 +1141,13 @@ inline bool pa_scatter_on_half_threads(const SlabGeom& sg) {
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, kPartThreads, 1>), \
                          grid, dim3(threads), hold, stream, __VA_ARGS__);            \
     else if (elem == 1)                                                                \
-      KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, __VA_ARGS__);          \
+      KVX_LAUNCH_TILES(KERNEL, PREFIX, 1, __VA_ARGS__);                                 \
     else if (elem == 2)                                                                \
-      KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 2, __VA_ARGS__);          \
+      KVX_LAUNCH_TILES(KERNEL, PREFIX, 2, __VA_ARGS__);                                 \
     else if (elem == 4)                                                                \
-      KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 4, __VA_ARGS__);          \
+      KVX_LAUNCH_TILES(KERNEL, PREFIX, 4, __VA_ARGS__);                                 \
     else                                                                               \
-      KVX_LAUNCH_HEADS(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, __VA_ARGS__);          \
+      KVX_LAUNCH_TILES(KERNEL, PREFIX, 8, __VA_ARGS__);                                 \
   } while (0)
 
 // LDS that a workgroup of a linear-walk scatter reserves, unused, so that six
@@ -989,38 +1180,47 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
   return hipSuccess;
 }
 
-// Launch the grouped kernel K<..., layout, kWave> of a copy of slabs of n16 vectors.
-#define KVX_LAUNCH_GROUPS(KERNEL, PREFIX, N16, ...)                                          \
+// Launch the grouped kernel of a copy of slabs of N16 vectors, GROUP of them per
+// workgroup (paged attention: an LDS image each).
+#define KVX_LAUNCH_GROUP(KERNEL, PREFIX, LAYOUT, ELEM, WAVE, LDS, ...)                      \
+  hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, WAVE>), grid,           \
+                     dim3(kPartThreads), LDS, stream, __VA_ARGS__)
+
+#define KVX_LAUNCH_GROUPS(KERNEL, PREFIX, N16, GROUP, ...)                                  \
   do {                                                                                 \
-    const dim3 tb(kPartThreads);                                                       \
     const bool wave = (N16) % 64 == 0;                                                 \
+    const size_t lds = 16u * (size_t)sg.image * (GROUP);                               \
     if (layout == KVX_LAYOUT_NHD && wave)                                              \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, true>), grid, tb, hold, stream, \
-                         __VA_ARGS__);                                                 \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, true, hold, __VA_ARGS__);     \
     else if (layout == KVX_LAYOUT_NHD)                                                 \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, false>), grid, tb, hold, stream, \
-                         __VA_ARGS__);                                                 \
-    else if (wave)                                                                     \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, true>), grid, tb, hold, stream, \
-                         __VA_ARGS__);                                                 \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, false, hold, __VA_ARGS__);    \
+    else if (layout == KVX_LAYOUT_HND && wave)                                         \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, true, hold, __VA_ARGS__);     \
+    else if (layout == KVX_LAYOUT_HND)                                                 \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, false, hold, __VA_ARGS__);    \
+    else if (elem == 1)                                                                \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, false, lds, __VA_ARGS__); \
+    else if (elem == 2)                                                                \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 2, false, lds, __VA_ARGS__); \
+    else if (elem == 4)                                                                \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 4, false, lds, __VA_ARGS__); \
     else                                                                               \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, false>), grid, tb, hold, stream, \
-                         __VA_ARGS__);                                                 \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, false, lds, __VA_ARGS__); \
   } while (0)
 
 template <bool kToPacked, bool kOrdered>
 hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
                   const OrderEntry* order, char* packed, int* err, int layout, int elem,
                   hipStream_t stream) {
+  const SlabGeom& sg = ug.sg;
   const size_t hold =
       !kToPacked && ug.linear_walk && ug.n16 >= kHeldMinVectors ? kLinearScatterLds : 0;
   if (ug.group > 1)
     return each_launch((ug.n_units - 1) / ug.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
       const dim3 grid(cnt);
-      KVX_LAUNCH_GROUPS(copy_unit_groups_kernel, (kToPacked, kOrdered), ug.n16, lp, bt, ug, group,
+      KVX_LAUNCH_GROUPS(copy_unit_groups_kernel, (kToPacked, kOrdered), ug.n16, ug.group, lp, bt, ug, group,
                         cnt, order, packed, err);
     });
-  const SlabGeom& sg = ug.sg;
   return each_launch(ug.n_units, ug.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_units_kernel, (kToPacked, kOrdered), lp, bt, ug, unit, part, cnt,
@@ -1032,14 +1232,14 @@ template <bool kToPacked>
 hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_ref* refs,
                          const ChunkGeom& cg, char* packed, int* err, int layout, int elem,
                          hipStream_t stream) {
+  const SlabGeom& sg = cg.sg;
   constexpr size_t hold = 0;
   if (cg.group > 1)
     return each_launch((cg.n_units - 1) / cg.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
       const dim3 grid(cnt);
-      KVX_LAUNCH_GROUPS(copy_chunk_groups_kernel, (kToPacked), cg.n16, lp, bt, refs, cg, group,
+      KVX_LAUNCH_GROUPS(copy_chunk_groups_kernel, (kToPacked), cg.n16, cg.group, lp, bt, refs, cg, group,
                         cnt, packed, err);
     });
-  const SlabGeom& sg = cg.sg;
   return each_launch(cg.n_units, cg.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, unit, part, cnt, packed, err);
@@ -1077,24 +1277,35 @@ uint32_t piece_vectors(uint32_t n16) {
   return ((n16 + parts - 1) / parts + 7u) & ~7u;
 }
 
-// Head shape and LDS layout for a reordering layout, from the stride (in
-// vectors) of the head's strided LDS reads: a gather (cache image in LDS)
+// Slab shape and LDS layout, from the stride (in vectors) of a tile's strided
+// LDS reads: a gather (cache image in LDS)
 // reads paged-attention K vectors and V elements of consecutive dims at
 // stride bs, and swizzles with shift log2 of that stride (at least 16)
 // rounded up to a power of two; a scatter (packed image in LDS) reads them at
-// stride v16 (K: consecutive tokens; V: the x tokens of one output vector)
-// and pads every v16 (at least 8) vectors. HND uses no LDS.
+// the stride of a tile's row (K: consecutive tokens; V: the x tokens of one
+// output vector) and pads after every row (of at least 8 vectors). HND uses
+// no LDS.
 SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   const uint32_t bs = (uint32_t)c->block_size, h = (uint32_t)c->num_kv_heads,
                  d = (uint32_t)c->head_dim, x = (uint32_t)(16 / c->elem_bytes),
                  v16 = (uint32_t)((int64_t)c->head_dim * c->elem_bytes / 16);
-  SlabGeom sg;
+  SlabGeom sg = {};
   sg.bs = fast_div(bs);
   sg.d = fast_div(d);
   sg.v16 = fast_div(v16 ? v16 : 1);
   sg.x = x;
   sg.nh = bs * v16;
   sg.prow = h * v16;
+  sg.heads = h;
+  if (c->layout == KVX_LAYOUT_PAGED_ATTN) {
+    const TileShape tile = paged_tile(bs, h, v16);
+    sg.gh = tile.heads;
+    sg.dw = tile.vectors;
+    sg.dpieces = fast_div(v16 / tile.vectors);
+    sg.row = fast_div(tile.heads * tile.vectors);
+    sg.np = fast_div(bs * tile.vectors);
+    sg.dwd = fast_div(tile.vectors);
+  }
   sg.piece = piece_vectors((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
   sg.n16 = fast_div((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
   sg.outer = fast_div(to_packed ? sg.prow : sg.nh);
@@ -1102,10 +1313,17 @@ SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   // V of 2-byte words as row pairs in a gather: token pairs, so an even
   // block size (v_pairs_gather says why not in a scatter)
   sg.v_pairs = c->elem_bytes == 2 && to_packed && bs % 2 == 0 ? 1u : 0u;
-  const uint32_t stride = to_packed ? bs : v16;
+  // transpose reads: a gather's 16-lane groups store 16 bytes of 16 tokens each,
+  // so four neighbouring groups must make up at least 64 bytes of every token
+  // (3 heads of 80 dims, five vectors a row: 651 us, by elements 388)
+  sg.v_bytes = c->elem_bytes == 1 && bs % 16 == 0 && (!to_packed || sg.dw % 4 == 0) ? 1u : 0u;
+  sg.bs16 = fast_div(bs / 16);
+  const uint32_t stride = to_packed ? bs : sg.row.d;
   sg.swz = 4;
   while ((1u << sg.swz) < stride) ++sg.swz;
   sg.pad = fast_div(stride < 8 ? 8 : stride);
+  const uint32_t n = sg.gh * sg.np.d;
+  sg.image = to_packed ? (n + 15u) & ~15u : n + n / sg.pad.d + 1;
   return sg;
 }
 
@@ -1174,7 +1392,7 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   ug.n16 = (uint32_t)(g.slab / 16);
   const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
   const int elem = cache->elem_bytes;
-  ug.group = copy_group(layout, ug.n16);
+  ug.group = copy_group(ug.n16);
   ug.parts = walk.parts;
   ug.parts_shift = walk.parts_shift;
   ug.parts_div = div_u32(ug.parts);
@@ -1255,8 +1473,8 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.n16 = (uint32_t)(slab / 16);
   const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
   const int elem = cache->elem_bytes;
-  copy_parts(layout, cg.n16, (uint32_t)cache->num_kv_heads, &cg.parts, &cg.parts_shift);
-  cg.group = copy_group(layout, cg.n16);
+  copy_parts(cache, cg.n16, &cg.parts, &cg.parts_shift);
+  cg.group = copy_group(cg.n16);
   cg.parts_div = div_u32(cg.parts);
   cg.upc_div = div_u32(cg.upc);
   cg.bpc_div = div_u32(cg.bpc);

@@ -15,17 +15,51 @@ uint32_t slab_pieces(int layout, uint32_t n16, uint32_t heads) {
 }
 
 int copy_layout(int layout, int32_t heads, int32_t block_size) {
-  if (layout == KVX_LAYOUT_HND && (heads == 1 || block_size == 1)) return KVX_LAYOUT_NHD;
+  if (block_size == 1 || (layout == KVX_LAYOUT_HND && heads == 1)) return KVX_LAYOUT_NHD;
   return layout;
 }
 
-void copy_parts(int layout, uint32_t n16, uint32_t heads, uint32_t* parts, uint32_t* shift) {
-  *parts = layout == KVX_LAYOUT_PAGED_ATTN ? heads : (n16 + kPartThreads - 1) / kPartThreads;
+// The tile that keeps most lanes of its workgroups busy, of
+//   - `g` whole neighbouring heads, up to 1,024 vectors, one, two or four a
+//     thread (a single 8-bit head of 16 tokens x 128 dims would fill half of a
+//     workgroup of one);
+//   - for a head that large, an even piece of its rows, at least a 128-byte line
+//     of the packed side wide, of at most 256 vectors.
+// Two and four vectors a thread count a little less, and rows that are not
+// whole lines much less unless the tile has all heads, so that its rows meet.
+TileShape paged_tile(uint32_t block_size, uint32_t heads, uint32_t v16) {
+  constexpr uint32_t kLine = 8;  // vectors
+  const uint32_t nh = block_size * v16;
+  if (heads * nh <= kPartThreads) return {heads, v16};
+  TileShape best = {1, v16};
+  float score = 0;
+  for (uint32_t g = 1; g <= heads && g * nh <= 4 * kPartThreads; ++g) {
+    const uint32_t v = g * nh <= kPartThreads ? 1 : g * nh <= 2 * kPartThreads ? 2 : 4;
+    const uint32_t tiles = (heads + g - 1) / g;
+    float f = (float)(heads * nh) / (float)(tiles * v * kPartThreads);
+    if (v > 1) f *= v == 2 ? 0.96f : 0.93f;
+    if (g < heads && g * v16 % kLine != 0) f *= 0.7f;
+    if (f > score) score = f, best = {g, v16};
+  }
+  for (uint32_t w = kLine; w < v16; w += kLine)
+    if (v16 % w == 0 && block_size * w <= kPartThreads &&
+        (float)(block_size * w) / kPartThreads > score)
+      score = (float)(block_size * w) / kPartThreads, best = {1, w};
+  return best;
+}
+
+void copy_parts(const kvx_cache* c, uint32_t n16, uint32_t* parts, uint32_t* shift) {
+  *parts = (n16 + kPartThreads - 1) / kPartThreads;
+  if (copy_layout(c->layout, c->num_kv_heads, c->block_size) == KVX_LAYOUT_PAGED_ATTN) {
+    const uint32_t v16 = (uint32_t)((int64_t)c->head_dim * c->elem_bytes / 16);
+    const TileShape t = paged_tile((uint32_t)c->block_size, (uint32_t)c->num_kv_heads, v16);
+    *parts = ((uint32_t)c->num_kv_heads + t.heads - 1) / t.heads * (v16 / t.vectors);
+  }
   *shift = (*parts & (*parts - 1)) == 0 ? (uint32_t)__builtin_ctz(*parts) : 32u;
 }
 
-uint32_t copy_group(int layout, uint32_t n16) {
-  return layout != KVX_LAYOUT_PAGED_ATTN && n16 <= kGroupMaxVectors ? kPartThreads / n16 : 1;
+uint32_t copy_group(uint32_t n16) {
+  return n16 <= kGroupMaxVectors ? kPartThreads / n16 : 1;
 }
 
 namespace {
@@ -145,13 +179,12 @@ kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g
   const uint32_t n16 = (uint32_t)(g.slab / 16), heads = (uint32_t)cache->num_kv_heads;
   w->pieces = slab_pieces(cache->layout, n16, heads);
   if ((uint64_t)g.n_units * w->pieces > 0x7FFFFFFF) return KVX_EINTERNAL;
-  const int layout = copy_layout(cache->layout, cache->num_kv_heads, cache->block_size);
-  copy_parts(layout, n16, heads, &w->parts, &w->parts_shift);
+  copy_parts(cache, n16, &w->parts, &w->parts_shift);
   const uint64_t n_work = (uint64_t)g.n_units * w->parts;
   // Pairs are chosen where both the pieces and the workgroups of a slab are a
   // power of two and slabs are not grouped.
   const uint32_t pair_parts =
-      w->pieces & (w->pieces - 1) || copy_group(layout, n16) > 1 ? 32u : w->parts_shift;
+      w->pieces & (w->pieces - 1) || copy_group(n16) > 1 ? 32u : w->parts_shift;
   const uint32_t n_slices = (uint32_t)(2 * g.lr);
   if (to_packed) {
     w->gather_pair_shift = gather_pairing(pair_parts, n_slices, (uint32_t)g.bpc,

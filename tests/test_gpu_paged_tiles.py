@@ -1,0 +1,116 @@
+"""Paged-attention tiles: several small heads per workgroup (with and without
+heads left over), one head, a head cut along its rows with one, two and four
+vectors a thread, a head that no piece of whole lines divides, and 8-bit
+transposes with blocks that are and are not a multiple of 16 tokens; gather and
+scatter in image and in destination order, and chunk lists. Everything is
+compared whole with the oracle."""
+import numpy as np
+import pytest
+
+import kvsynth
+import oracle
+from kvtest_util import Filled, device_cache, first_mismatch, host_mirror, seeded_ids, to_host
+
+torch = pytest.importorskip("torch")
+import paper_2609_11744_amd as kvx  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+PA = oracle.LAYOUT_PAGED_ATTN
+
+SHAPES = [
+    # (block, heads, dim, elem): tile
+    (16, 8, 128, 1),    # two heads of 128 vectors
+    (16, 5, 128, 1),    # the same, one head left over
+    (16, 3, 96, 1),     # two heads of 96, one left over
+    (16, 4, 64, 1),     # four heads of 64
+    (16, 7, 64, 2),     # two heads of 128, one left over
+    (8, 3, 80, 2),      # three heads of 80
+    (8, 5, 64, 1),      # five heads of 32 (all the slab)
+    (16, 1, 128, 1),    # one head of 128
+    (8, 1, 64, 1),      # one head of 32: a 512-byte slab
+    (1, 3, 48, 2),      # one token a block
+    (16, 2, 256, 2),    # 512 vectors a head: rows cut in halves
+    (32, 4, 128, 2),    # the same with 32 tokens
+    (32, 2, 96, 2),     # 384 vectors: no even line piece, two a thread
+    (64, 2, 128, 2),    # 1,024 vectors: halves, two a thread
+    (128, 1, 128, 2),   # 2,048 vectors: halves, four a thread
+    (160, 1, 128, 2),   # 2,560: twelve a thread
+    (64, 3, 128, 1),    # 512 vectors, two a thread
+    (32, 3, 128, 1),    # 256 vectors
+    (48, 2, 80, 1),     # 240 vectors
+    (24, 2, 128, 1),    # 8-bit, 24 tokens a block
+    (20, 2, 64, 1),     # 8-bit, 20 tokens
+    (16, 3, 80, 4),     # 4-byte words: 320 vectors a head
+    (8, 2, 256, 4),     # 512 vectors, halves
+    (4, 3, 32, 8),      # 8-byte words
+]
+
+
+def _bt(ids):
+    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(DEV)
+
+
+def _setup(shape, L, NB, seed):
+    bs, h, d, e = shape
+    s = oracle.Shape(L, NB, bs, h, d, e, PA)
+    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
+    return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
+
+
+def _same_cache(cache, mirror, L):
+    torch.cuda.synchronize()
+    for l in range(L):
+        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
+        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"p{i}" for i in range(len(SHAPES))])
+@pytest.mark.parametrize("n,bpc", [(11, 4), (1027, 16)])
+def test_paged_tiles_bit_exact(shape, n, bpc):
+    L, l0, l1 = (3, 1, 3) if n < 100 else (1, 0, 1)
+    bs = shape[0]
+    NB = 2 * n + 5
+    s, cache, mirror = _setup(shape, L, NB, 700 + n)
+    src, dst_ids = seeded_ids(700 + n, NB, n, n)
+    expect = oracle.gather(s, *mirror, l0, l1, src, bpc * bs)
+    out = torch.full((expect.size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_blocks(cache, l0, l1, _bt(src), n, bpc * bs, out)
+    kvx.kvx_check()
+    got = to_host(out)
+    assert first_mismatch(got[:expect.size], expect) is None
+    assert (got[expect.size:] == 0xA5).all()
+    kvx.kvx_scatter_blocks(cache, l0, l1, _bt(dst_ids), n, bpc * bs, out)
+    kvx.kvx_check()
+    oracle.scatter(s, *mirror, l0, l1, dst_ids, bpc * bs, expect)
+    _same_cache(cache, mirror, L)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"p{i}" for i in range(len(SHAPES))])
+def test_paged_tile_chunk_lists_bit_exact(shape):
+    L, bpc = 2, 5
+    bs = shape[0]
+    sizes = [5, 1, 3, 5, 2, 4]
+    n = sum(sizes)
+    NB = 2 * n + 3
+    s, cache, mirror = _setup(shape, L, NB, 800)
+    src, dst_ids = seeded_ids(800, NB, n, n)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    refs, at, off = [], 0, 48
+    for m in sizes:
+        refs.append((off, at, m))
+        at, off = at + m, off + m * per_block + 32
+    rd = kvx.chunk_refs(refs, DEV)
+    out = torch.full((off,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(src), n, rd, len(refs), bpc * bs, out)
+    kvx.kvx_check()
+    want = np.full(off, 0xA5, np.uint8)
+    images = [oracle.gather(s, *mirror, 0, L, src[a:a + m], m * bs) for _, a, m in refs]
+    for (o, _, _), img in zip(refs, images):
+        want[o:o + img.size] = img
+    assert first_mismatch(to_host(out), want) is None
+    kvx.kvx_scatter_chunks(cache, 0, L, _bt(dst_ids), n, rd, len(refs), bpc * bs, out)
+    kvx.kvx_check()
+    for (_, a, m), img in zip(refs, images):
+        oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, img)
+    _same_cache(cache, mirror, L)
