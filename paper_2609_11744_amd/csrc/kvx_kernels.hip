@@ -347,8 +347,11 @@ struct Tile {
   uint32_t heads;
 };
 
+// kOne, here and below: the tile is one whole head (the usual shapes), which
+// spares each lane the split by head.
+template <bool kOne>
 __device__ __forceinline__ Tile tile_at(uint32_t part, const SlabGeom& g) {
-  if (g.gh == 1 && g.dpieces.d == 1) return Tile{part * g.nh, part * g.v16.d, 1};
+  if (kOne) return Tile{part * g.nh, part * g.v16.d, 1};
   uint32_t piece;
   const uint32_t group = divmod(part, g.dpieces, piece), h0 = group * g.gh;
   const uint32_t left = g.heads - h0;
@@ -358,27 +361,28 @@ __device__ __forceinline__ Tile tile_at(uint32_t part, const SlabGeom& g) {
 // Vector w of the tile in packed order (token by token, then head, then
 // vector): its packed-side offset from the tile's first vector; ok = false for
 // a head the slab does not have.
+template <bool kOne>
 __device__ __forceinline__ uint32_t packed_at(uint32_t w, const SlabGeom& g, const Tile& tile,
                                               bool* ok) {
   uint32_t q;
   const uint32_t t = divmod(w, g.row, q);
-  *ok = t < g.bs.d && q < tile.heads * g.dw;
+  *ok = kOne ? w < g.nh : t < g.bs.d && q < tile.heads * g.dw;
   return t * g.prow + q;
 }
 
 // The same offset in the direction's destination or source order: the cache
 // side is contiguous.
-template <bool kPackedSide>
+template <bool kPackedSide, bool kOne>
 __device__ __forceinline__ uint32_t side_at(uint32_t w, const SlabGeom& g, const Tile& tile,
                                             bool* ok) {
-  if (kPackedSide) return packed_at(w, g, tile, ok);
-  *ok = w < tile.heads * g.np.d;
+  if (kPackedSide) return packed_at<kOne>(w, g, tile, ok);
+  *ok = w < (kOne ? g.nh : tile.heads * g.np.d);
   return w;
 }
 
 // Load the tile's source vectors, in source order, into the LDS image. A gather
 // reads the cache (contiguous), a scatter the packed rows.
-template <bool kToPacked, int kElem, int T, int V>
+template <bool kToPacked, int kElem, bool kOne, int T, int V>
 __device__ __forceinline__ void stage_in(const v4u* __restrict__ src, const SlabGeom& g,
                                          const Tile& tile) {
   v4u* lds = reinterpret_cast<v4u*>(kvx_lds);
@@ -386,7 +390,7 @@ __device__ __forceinline__ void stage_in(const v4u* __restrict__ src, const Slab
   bool ok[V];
 #pragma unroll
   for (int q = 0; q < V; ++q) {
-    const uint32_t at = side_at<!kToPacked>(threadIdx.x + q * T, g, tile, &ok[q]);
+    const uint32_t at = side_at<!kToPacked, kOne>(threadIdx.x + q * T, g, tile, &ok[q]);
     if (ok[q]) r[q] = __builtin_nontemporal_load(src + at);
   }
 #pragma unroll
@@ -417,7 +421,7 @@ __device__ __forceinline__ uint32_t tile_dst_bytes(const SlabGeom& g) {
 
 // Write the tile's destination vectors, in destination order, each produced by
 // f(w). A gather writes the packed rows, a scatter the cache.
-template <bool kToPacked, int T, int V, typename F>
+template <bool kToPacked, bool kOne, int T, int V, typename F>
 __device__ __forceinline__ void stage_out(v4u* __restrict__ dst, const SlabGeom& g,
                                           const Tile& tile, F f) {
   v4u r[V];
@@ -425,7 +429,7 @@ __device__ __forceinline__ void stage_out(v4u* __restrict__ dst, const SlabGeom&
   bool ok[V];
 #pragma unroll
   for (int q = 0; q < V; ++q) {
-    at[q] = side_at<kToPacked>(threadIdx.x + q * T, g, tile, &ok[q]);
+    at[q] = side_at<kToPacked, kOne>(threadIdx.x + q * T, g, tile, &ok[q]);
     if (ok[q]) r[q] = f(threadIdx.x + q * T);
   }
   const auto out = stream_dst(dst, tile_dst_bytes<kToPacked>(g));
@@ -436,28 +440,30 @@ __device__ __forceinline__ void stage_out(v4u* __restrict__ dst, const SlabGeom&
 
 // Head and rest of a tile's vector: index in packed order -> (token, head of the
 // tile, vector of the head's row); in cache order -> (head, vector of the head).
+template <bool kOne>
 __device__ __forceinline__ void packed_split(uint32_t w, const SlabGeom& g, uint32_t* t,
                                              uint32_t* h, uint32_t* dv) {
   *t = divmod(w, g.row, *dv);
   *h = 0;
-  if (g.gh > 1) *h = divmod(*dv, g.dwd, *dv);
+  if (!kOne) *h = divmod(*dv, g.dwd, *dv);
 }
 
+template <bool kOne>
 __device__ __forceinline__ uint32_t cache_split(uint32_t w, const SlabGeom& g, uint32_t* r) {
   *r = w;
-  return g.gh > 1 ? divmod(w, g.np, *r) : 0;
+  return kOne ? 0 : divmod(w, g.np, *r);
 }
 
 // Paged-attention K: source vector (in the LDS image) of destination vector w.
 // Cache order inside a head is dv * bs + t, packed order (t, head, dv).
-template <bool kToPacked>
+template <bool kToPacked, bool kOne>
 __device__ __forceinline__ uint32_t k_source(uint32_t w, const SlabGeom& g) {
   uint32_t t, h, dv, r;
   if (kToPacked) {
-    packed_split(w, g, &t, &h, &dv);
+    packed_split<kOne>(w, g, &t, &h, &dv);
     return h * g.np.d + dv * g.bs.d + t;
   }
-  h = cache_split(w, g, &r);
+  h = cache_split<kOne>(w, g, &r);
   dv = divmod(r, g.bs, t);
   return t * g.row.d + h * g.dw + dv;
 }
@@ -470,14 +476,14 @@ struct ElemRow {
 // Paged-attention V: destination vector w assembled element by element from
 // the LDS image of the source. Cache elements inside a head are (dim, t) at
 // dim * bs + t; packed elements (t, head, dim).
-template <bool kToPacked, typename E>
+template <bool kToPacked, bool kOne, typename E>
 __device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g,
                                           const unsigned char* image) {
   constexpr uint32_t kX = 16 / sizeof(E);
   ElemRow<E> out;
   if (kToPacked) {  // packed (t, dv * x + i) <- cache element (dv * x + i, t): stride bs
     uint32_t t, h, dv;
-    packed_split(w, g, &t, &h, &dv);
+    packed_split<kOne>(w, g, &t, &h, &dv);
     const uint32_t e0 = (h * g.np.d + dv * g.bs.d) * kX + t;
 #pragma unroll
     for (uint32_t i = 0; i < kX; ++i) {
@@ -487,7 +493,7 @@ __device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g,
     }
   } else {  // cache (dim, t .. t + x - 1) <- packed elements (t + i, dim); t wraps to dim + 1
     uint32_t r, t;
-    const uint32_t h = cache_split(w, g, &r);
+    const uint32_t h = cache_split<kOne>(w, g, &r);
     uint32_t dim = h * g.dw * kX + divmod(r * kX, g.bs, t);
 #pragma unroll
     for (uint32_t i = 0; i < kX; ++i) {
@@ -514,7 +520,7 @@ __device__ __forceinline__ v4u v_elements(uint32_t w, const SlabGeom& g,
 // write every other 32-byte run of the cache lines (the 80k scatter ran at
 // half speed that way). Pairs take half of a tile's threads, so a thread has
 // (V + 1) / 2 of them.
-template <int T, int V>
+template <bool kOne, int T, int V>
 __device__ __forceinline__ void v_pairs_gather(v4u* __restrict__ dst, const SlabGeom& g,
                                                const Tile& tile) {
   typedef ElemRow<uint16_t> Row;
@@ -527,8 +533,8 @@ __device__ __forceinline__ void v_pairs_gather(v4u* __restrict__ dst, const Slab
     // a half-wave takes 4 token pairs x 8 dim groups (16 vectors per row)
     const uint32_t p = lane_perm(threadIdx.x + q * T);
     uint32_t tp, h, dv;
-    packed_split(p, g, &tp, &h, &dv);  // tokens 2 tp, 2 tp + 1
-    ok[q] = 2 * tp < g.bs.d && h < tile.heads;
+    packed_split<kOne>(p, g, &tp, &h, &dv);  // tokens 2 tp, 2 tp + 1
+    ok[q] = kOne ? 2 * p < g.nh : 2 * tp < g.bs.d && h < tile.heads;
     if (!ok[q]) continue;
     at[q] = 2 * tp * g.prow + h * g.dw + dv;
     const uint32_t e0 = (h * g.np.d + dv * g.bs.d) * 8 + 2 * tp;
@@ -614,7 +620,7 @@ __device__ __forceinline__ void v_bytes_out(v4u* __restrict__ dst, const SlabGeo
 
 // One tile of a paged-attention slab (pv, pk: the slab's first vector on the
 // cache and on the packed side).
-template <bool kToPacked, int kElem, int T, int V>
+template <bool kToPacked, int kElem, bool kOne, int T, int V>
 __device__ __forceinline__ void move_tile(v4u* pv, v4u* pk, const SlabGeom& g, uint32_t kv,
                                           uint32_t part) {
   typedef typename std::conditional<
@@ -622,28 +628,29 @@ __device__ __forceinline__ void move_tile(v4u* pv, v4u* pk, const SlabGeom& g, u
       typename std::conditional<kElem == 2, uint16_t,
                                 typename std::conditional<kElem == 4, uint32_t,
                                                           uint64_t>::type>::type>::type E;
-  const Tile tile = tile_at(part, g);
+  const Tile tile = tile_at<kOne>(part, g);
   const v4u* src = kToPacked ? pv + tile.cache0 : pk + tile.packed0;
   v4u* dst = kToPacked ? pk + tile.packed0 : pv + tile.cache0;
-  stage_in<kToPacked, kElem, T, V>(src, g, tile);
+  stage_in<kToPacked, kElem, kOne, T, V>(src, g, tile);
   __syncthreads();
   const v4u* lds = reinterpret_cast<const v4u*>(kvx_lds);
   if (kv == 0)
-    stage_out<kToPacked, T, V>(dst, g, tile, [&](uint32_t w) {
-      return lds[lds_slot<kToPacked, kElem>(k_source<kToPacked>(w, g), g)];
+    stage_out<kToPacked, kOne, T, V>(dst, g, tile, [&](uint32_t w) {
+      return lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, kOne>(w, g), g)];
     });
   else if (kElem == 1 && g.v_bytes)
     v_bytes_out<kToPacked, T, V>(dst, g, tile);
   else if (kToPacked && kElem == 2 && g.v_pairs)
-    v_pairs_gather<T, V>(dst, g, tile);
+    v_pairs_gather<kOne, T, V>(dst, g, tile);
   else
-    stage_out<kToPacked, T, V>(
-        dst, g, tile, [&](uint32_t w) { return v_elements<kToPacked, E>(w, g, kvx_lds); });
+    stage_out<kToPacked, kOne, T, V>(dst, g, tile, [&](uint32_t w) {
+      return v_elements<kToPacked, kOne, E>(w, g, kvx_lds);
+    });
 }
 
 // Move part `part` of one slab in the direction and layout of the kernel: a
 // 4 KiB piece with the default layout and HND, one tile with paged attention.
-template <bool kToPacked, int kLayout, int kElem, int T, int V>
+template <bool kToPacked, int kLayout, int kElem, bool kOne, int T, int V>
 __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, const SlabGeom& g,
                                           uint32_t kv, uint32_t part) {
   v4u* pv = reinterpret_cast<v4u*>(paged);
@@ -662,7 +669,7 @@ __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, c
     else
       move_rows(kv4, pv, n16, g, part);
   } else {
-    move_tile<kToPacked, kElem, T, V>(pv, kv4, g, kv, part);
+    move_tile<kToPacked, kElem, kOne, T, V>(pv, kv4, g, kv, part);
   }
 }
 
@@ -685,7 +692,7 @@ __device__ __forceinline__ uint32_t split_work(uint32_t w, uint32_t parts, uint3
 // and waited for once. The empty asm statements take the loaded values,
 // which keeps the compiler from moving the layer pointer's load past the
 // block-id check.
-template <bool kToPacked, bool kOrdered, int kLayout, int kElem, int T, int V>
+template <bool kToPacked, bool kOrdered, int kLayout, int kElem, bool kOne, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_units_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table, UnitGeom g,
                       uint32_t unit_base, uint32_t part_base, uint32_t work_count,
@@ -751,7 +758,7 @@ __global__ void __launch_bounds__(T)
   }
   char* paged = layer + (uint64_t)(uint32_t)id * g.slab;
   char* pk = packed + (uint64_t)u * g.slab;
-  move_unit<kToPacked, kLayout, kElem, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
+  move_unit<kToPacked, kLayout, kElem, kOne, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
 }
 
 // Chunk-list copy: a batch of chunks, each with its own block-table slice and
@@ -788,7 +795,7 @@ __device__ __forceinline__ bool chunk_ref_ok(const kvx_chunk_ref& ref, const Chu
          ref.packed_offset + (int64_t)g.lr2 * ref.n_blocks * (int64_t)g.slab <= g.packed_bytes;
 }
 
-template <bool kToPacked, int kLayout, int kElem, int T, int V>
+template <bool kToPacked, int kLayout, int kElem, bool kOne, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_chunks_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
                        const kvx_chunk_ref* __restrict__ refs, ChunkGeom g, uint32_t unit_base,
@@ -816,7 +823,7 @@ __global__ void __launch_bounds__(T)
   }
   char* paged = layers.p[lk] + (uint64_t)(uint32_t)id * g.slab;
   char* pk = packed + ref.packed_offset + (uint64_t)(lk * nc + j) * g.slab;
-  move_unit<kToPacked, kLayout, kElem, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
+  move_unit<kToPacked, kLayout, kElem, kOne, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
 }
 
 // ---- small slabs: several per workgroup ----------------------------------------
@@ -902,11 +909,11 @@ __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, u
   if (!p.ok) return;
   v4u v;
   if (p.kv == 0)
-    v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked>(w, g), g)];
+    v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
   else if (kElem == 1 && g.v_bytes)
     v = v_bytes<kToPacked>(w, g, image, &w);
   else
-    v = v_elements<kToPacked, E>(w, g, image);
+    v = v_elements<kToPacked, false, E>(w, g, image);
   store_grouped<false>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
 }
 
@@ -1107,38 +1114,44 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
 // heads per slab on half the threads (pa_scatter_on_half_threads; the gather
 // was no faster that way). PREFIX is the kernel's parenthesized leading
 // template arguments; kToPacked is the enclosing launcher's direction.
-#define KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, V, ...)                                    \
-  hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, T, V>), grid, \
+#define KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, ONE, T, V, ...)                               \
+  hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, ONE, T, V>), grid, \
                      dim3(T), tile_lds(sg, T, V), stream, __VA_ARGS__)
 
 #define KVX_LAUNCH_TILES(KERNEL, PREFIX, ELEM, ...)                                         \
   do {                                                                                 \
     const uint32_t n = sg.gh * sg.np.d;                                                \
+    const bool one = sg.gh == 1 && sg.dpieces.d == 1;                                  \
     constexpr int T = kTransposeThreads;                                               \
     if constexpr (!kToPacked) {                                                        \
       if (pa_scatter_on_half_threads(sg)) {                                            \
-        KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T / 2, 2, __VA_ARGS__);                  \
+        if (one)                                                                       \
+          KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, true, T / 2, 2, __VA_ARGS__);          \
+        else                                                                           \
+          KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T / 2, 2, __VA_ARGS__);         \
         break;                                                                         \
       }                                                                                \
     }                                                                                  \
-    if (n <= (uint32_t)T)                                                              \
-      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 1, __VA_ARGS__);                        \
+    if (n <= (uint32_t)T && one)                                                       \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, true, T, 1, __VA_ARGS__);                  \
+    else if (n <= (uint32_t)T)                                                         \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 1, __VA_ARGS__);                 \
     else if (n <= 2u * T)                                                              \
-      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 2, __VA_ARGS__);                        \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 2, __VA_ARGS__);                 \
     else if (n <= 4u * T)                                                              \
-      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, 4, __VA_ARGS__);                        \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 4, __VA_ARGS__);                 \
     else                                                                               \
-      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, T, kVecPerThread, __VA_ARGS__);            \
+      KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, kVecPerThread, __VA_ARGS__);     \
   } while (0)
 
 #define KVX_DISPATCH(KERNEL, PREFIX, ...)                                                   \
   do {                                                                                 \
     const uint32_t threads = (sg.piece + 63u) & ~63u;                                  \
     if (layout == KVX_LAYOUT_NHD)                                                      \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, kPartThreads, 1>), \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, false, kPartThreads, 1>), \
                          grid, dim3(threads), hold, stream, __VA_ARGS__);            \
     else if (layout == KVX_LAYOUT_HND)                                                 \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, kPartThreads, 1>), \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, false, kPartThreads, 1>), \
                          grid, dim3(threads), hold, stream, __VA_ARGS__);            \
     else if (elem == 1)                                                                \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 1, __VA_ARGS__);                                 \
