@@ -160,18 +160,17 @@ kvx_status kvx_scatter_blocks(const kvx_cache* cache, int32_t l0, int32_t l1,
  * NULL. A call moves work_items pieces of slabs, parts per slab (4 KiB pieces
  * with the default layout, heads with the others); a workgroup moves one piece,
  * or where pieces are small several, or a share of a large one. A scatter of
- * 1,024 blocks or more in chunks of more than one block runs in ascending
- * destination order (ordered = 1; block ids bucketed by a small kernel first),
- * except with slabs of at most 8 KiB in the default layout (or a reordering
+ * 1,024 blocks or more over more than one layer, in chunks of more than one
+ * block, runs in ascending destination order (ordered = 1; block ids bucketed
+ * by a small kernel first), except with slabs of at most 8 KiB in the default layout (or a reordering
  * layout with one KV head): those, like every smaller scatter, walk the packed
  * image in order, with linear = 1 (slabs that divide 4 KiB or are a multiple
  * of it) when the b-th workgroup moves the b-th share of the image rather than
  * each XCD taking one contiguous range. pair_slices = D > 0: slices D apart,
  * whose runs sit 2 MiB apart in a packed chunk, are moved together (the
  * gather's paired walk, or an ordered scatter's two fronts per XCD: fronts =
- * 2). For an
- * empty call every field is 0. KVX_EINVAL for the
- * arguments the copy calls reject on the host (except pointers). */
+ * 2). For an empty call every field is 0. KVX_EINVAL for the arguments the copy
+ * calls reject on the host (except pointers). */
 typedef struct kvx_walk {
   int64_t work_items;
   int32_t parts;
@@ -225,6 +224,8 @@ typedef struct kvx_chunk_ref {
  *   block_table  device int32[table_len]
  *   packed       device, 16-byte aligned, packed_bytes bytes; must not
  *                overlap any cache tensor
+ * A list of mostly short chunks, by n_chunks, chunk_tokens and table_len, takes
+ * stream-ordered scratch for the call, except on a capturing stream.
  * Host-checkable errors as for kvx_gather_blocks (KVX_EINVAL), plus a launch
  * too large for 32-bit unit indexes (n_chunks * (l1 - l0) * 2 * blocks per
  * chunk >= 2^31). The refs live on the device and are checked by the kernel:

@@ -773,6 +773,9 @@ struct ChunkGeom {
   uint32_t upc;          // (l1 - l0) * 2 * bpc
   uint32_t bpc;
   uint32_t lr2;          // (l1 - l0) * 2
+  uint32_t n_chunks;
+  uint32_t list_grid;    // workgroups of a copy without padding (copy_list_kernel)
+  DivU32 lr2_div;
   uint32_t num_blocks;   // pool size
   uint32_t n_units;      // n_chunks * upc
   uint32_t n16;
@@ -824,6 +827,152 @@ __global__ void __launch_bounds__(T)
   char* paged = layers.p[lk] + (uint64_t)(uint32_t)id * g.slab;
   char* pk = packed + ref.packed_offset + (uint64_t)(lk * nc + j) * g.slab;
   move_unit<kToPacked, kLayout, kElem, kOne, T, V>(paged, pk, g.n16, g.sg, lk & 1, part);
+}
+
+// ---- chunk lists without padding ----------------------------------------------
+//
+// Where many of a list's chunks are short, the padded unit space above dispatches
+// a workgroup for every piece that they do not have, and its equal ranges of
+// units give the XCDs unequal bytes. list_kernel therefore writes one ListBlock
+// per block that the list does have, in list order; the copy's units are then
+// 0 .. lr2 * blocks - 1, chunk by chunk, and unit u belongs to the chunk of block
+// u / lr2. (A search for the chunk in every 4 KiB workgroup, the other way to find
+// it, would put several dependent loads before the data.) Decode and loads are as
+// many as in the padded space. A gather moves slices 2 MiB apart in a chunk
+// together, as in the unit walk (gather_pairing), where the chunk's own length
+// puts them there. 1 GiB in chunks of 1 to 16 of 16 blocks, 32 layers, gather /
+// scatter, padded -> listed: 32 KiB slabs 389 / 401 -> 354 / 378 us; of 64 blocks
+// 487 / 498 -> 358 / 382; 80 layers of 4 KiB slabs 401 / 413 -> 359 / 388; 256 MiB
+// of 32 KiB slabs 116 / 120 -> 94 / 100.
+
+// What a unit's decode needs of the chunk that holds its block.
+struct ListBlock {
+  int64_t packed;   // the chunk's packed_offset
+  uint32_t first;   // blocks of the list before the chunk
+  uint32_t n;       // blocks of the chunk, and the multiplier and shift of DivU32 for n
+  uint32_t m, s;
+  int32_t bt;       // the chunk's bt_offset
+  uint32_t pair;    // log2 of the distance of its paired slices, or 32
+};
+static_assert(sizeof(ListBlock) == 32, "one scalar load");
+
+constexpr uint32_t kListThreads = 256;
+constexpr uint32_t kListChunks = 64;    // chunks per workgroup of list_kernel
+constexpr uint32_t kListMaxChunks = 4096;  // each workgroup sums the blocks of all chunks before its own
+constexpr uint64_t kListMaxBlocks = 1u << 21;  // 64 MiB of entries
+
+// Blocks of chunk c, or 0 for a bad reference.
+__device__ __forceinline__ uint32_t list_blocks(const kvx_chunk_ref* refs, uint32_t c,
+                                                const ChunkGeom& g) {
+  const kvx_chunk_ref ref = refs[c];
+  return chunk_ref_ok(ref, g) ? (uint32_t)ref.n_blocks : 0u;
+}
+
+// blocks[0 .. *count) for the list; bad references are reported and left out.
+// pair: 1 if the slices of a chunk may be paired.
+__global__ void __launch_bounds__(kListThreads)
+    list_kernel(const kvx_chunk_ref* __restrict__ refs, ChunkGeom g, uint32_t pair,
+                ListBlock* __restrict__ blocks, uint32_t* __restrict__ count,
+                int* __restrict__ err) {
+  __shared__ uint32_t before_wave[kListThreads / 64];
+  __shared__ uint32_t end[kListChunks];  // blocks of this workgroup's chunks up to and with c
+  const uint32_t t = threadIdx.x, c0 = blockIdx.x * kListChunks;
+  const uint32_t nc = g.n_chunks - c0 < kListChunks ? g.n_chunks - c0 : kListChunks;
+  uint32_t sum = 0;
+  for (uint32_t c = t; c < c0; c += kListThreads) sum += list_blocks(refs, c, g);
+  for (uint32_t off = 32; off; off >>= 1) sum += __shfl_down(sum, off, 64);
+  if (t % 64 == 0) before_wave[t / 64] = sum;
+  if (t < 64) {
+    uint32_t n = t < nc ? list_blocks(refs, c0 + t, g) : 0u;
+    if (t < nc && n == 0) atomicOr(err, kErrBadChunk);
+    for (uint32_t off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(n, off, 64);
+      if (t >= off) n += y;
+    }
+    end[t] = n;
+  }
+  __syncthreads();
+  uint32_t before = 0;
+  for (uint32_t w = 0; w < kListThreads / 64; ++w) before += before_wave[w];
+  const uint32_t mine = end[nc - 1];
+  if (t == 0 && c0 + nc == g.n_chunks) *count = before + mine;
+  for (uint32_t k = t; k < mine; k += kListThreads) {
+    uint32_t lo = 0, hi = nc - 1;  // the first chunk whose end is above k
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) / 2;
+      if (end[mid] > k) hi = mid;
+      else lo = mid + 1;
+    }
+    const kvx_chunk_ref ref = refs[c0 + lo];
+    ListBlock b;
+    b.packed = ref.packed_offset;
+    b.first = before + (lo ? end[lo - 1] : 0u);
+    b.n = (uint32_t)ref.n_blocks;
+    uint32_t l = 0;  // ceil(log2 n), as div_u32
+    while ((1ull << l) < b.n) ++l;
+    b.m = b.n <= 1 ? 0u : (uint32_t)(((1ull << 32) * ((1ull << l) - b.n)) / b.n + 1);
+    b.s = b.n <= 1 ? 0u : l - 1;
+    b.bt = ref.bt_offset;
+    b.pair = 32;
+    const uint64_t run = (uint64_t)b.n * g.slab, two_mib = 2u << 20;
+    if (pair && two_mib % run == 0) {
+      const uint32_t d = (uint32_t)(two_mib / run);  // as gather_pairing
+      if ((d & (d - 1)) == 0 && d <= 32 && g.lr2 % (2 * d) == 0) b.pair = 31 - __clz(d);
+    }
+    blocks[before + k] = b;
+  }
+}
+
+// The copy over blocks[0 .. *count): as many workgroups as the table has entries
+// for, which is as many as the list needs unless its chunks share entries. Then
+// workgroups go round again, with paged attention (kLoop = false) those of a
+// second launch from workgroup `first` on, which else end at once: around the
+// LDS phases the loop cost 8 to 25 % (8 x 128 dims, 1 GiB, uneven lists, gather /
+// scatter: bf16 389 / 398 us looped, 357 / 397 in two launches; 8-bit 423 / 510
+// and 372 / 402), around plain moves nothing.
+template <bool kToPacked, bool kLoop, int kLayout, int kElem, bool kOne, int T, int V>
+__global__ void __launch_bounds__(T)
+    copy_list_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
+                     const ListBlock* __restrict__ blocks, const uint32_t* __restrict__ count,
+                     ChunkGeom g, uint32_t first, uint32_t stride, char* __restrict__ packed,
+                     int* __restrict__ err) {
+  constexpr bool kAgain = kLoop || kLayout != KVX_LAYOUT_PAGED_ATTN;
+  const uint32_t total = *count * g.lr2 * g.parts;
+  uint32_t b = first + blockIdx.x;
+  if (b >= total) return;
+  do {
+    uint32_t part;
+    const uint32_t u =
+        split_work(xcd_contiguous(b, total), g.parts, g.parts_shift, g.parts_div, &part);
+    const ListBlock e = blocks[divu(u, g.lr2_div)];
+    const uint32_t r = u - e.first * g.lr2;
+    const DivU32 nd{e.n, e.m, e.s};
+    uint32_t lk, j;
+    if (kToPacked && e.pair < 32) {  // the paired walk of copy_units_kernel
+      const uint32_t ps = g.parts_shift + 1;
+      const uint32_t wi = (r << g.parts_shift) + part, p = divu(wi >> ps, nd);
+      const uint32_t r2 = wi - ((p * e.n) << ps), r3 = r2 & ((1u << ps) - 1);
+      j = r2 >> ps;
+      part = r3 >> 1;
+      lk = ((p >> e.pair) << (e.pair + 1)) + (p & ((1u << e.pair) - 1)) + ((r3 & 1) << e.pair);
+    } else {
+      lk = divu(r, nd);
+      j = r - lk * e.n;
+    }
+    const int32_t id = block_table[e.bt + (int32_t)j];
+    char* layer = layers.p[lk];
+    __asm__ volatile("" : : "s"(id), "s"(layer));
+    if ((uint32_t)id < g.num_blocks) {
+      char* pk = packed + e.packed + (uint64_t)(lk * e.n + j) * g.slab;
+      move_unit<kToPacked, kLayout, kElem, kOne, T, V>(layer + (uint64_t)(uint32_t)id * g.slab, pk,
+                                                       g.n16, g.sg, lk & 1, part);
+    } else if (threadIdx.x == 0) {
+      atomicOr(err, kErrBadBlock);
+    }
+    if (!kAgain) return;
+    if (kLayout == KVX_LAYOUT_PAGED_ATTN) __syncthreads();  // before the LDS image is reused
+    b += stride;
+  } while (b < total);
 }
 
 // ---- small slabs: several per workgroup ----------------------------------------
@@ -1017,6 +1166,46 @@ __global__ void __launch_bounds__(kPartThreads)
     move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
 
+// The grouped copy over a list without padding.
+template <bool kToPacked, bool kLoop, int kLayout, int kElem, bool kWave>
+__global__ void __launch_bounds__(kPartThreads)
+    copy_list_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
+                            const ListBlock* __restrict__ blocks,
+                            const uint32_t* __restrict__ count, ChunkGeom g, uint32_t first,
+                            uint32_t stride, char* __restrict__ packed, int* __restrict__ err) {
+  constexpr bool kAgain = kLoop || kLayout != KVX_LAYOUT_PAGED_ATTN;
+  const uint32_t units = *count * g.lr2, groups = (units + g.group - 1) / g.group;
+  uint32_t w;
+  const uint32_t i = grouped_unit<kWave>(g.sg, &w);
+  uint32_t b = first + blockIdx.x;
+  if (b >= groups) return;
+  do {
+    const uint32_t u = xcd_contiguous(b, groups) * g.group + i;
+    Place p = {};
+    if (i < g.group && u < units) {
+      const ListBlock e = blocks[divu(u, g.lr2_div)];
+      const uint32_t r = u - e.first * g.lr2, lk = divu(r, DivU32{e.n, e.m, e.s});
+      const uint32_t j = r - lk * e.n;
+      const int32_t id = block_table[e.bt + (int32_t)j];
+      char* layer = layers.p[lk];
+      p.ok = (uint32_t)id < g.num_blocks;
+      if (!p.ok && w == 0) atomicOr(err, kErrBadBlock);
+      p.paged = layer + (uint64_t)(uint32_t)id * g.slab;
+      p.packed = packed + e.packed + (uint64_t)r * g.slab;
+      p.base = kToPacked ? packed : layer;
+      p.kv = lk & 1;
+    }
+    if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN) {
+      move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+      if (!kAgain) return;
+      __syncthreads();  // before the LDS images are reused
+    } else if (p.ok) {
+      move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
+    }
+    b += stride;
+  } while (b < groups);
+}
+
 // Destination order for a scatter: order[] lists the block-table indexes,
 // each with the id it holds, bucketed by destination id, buckets ascending. The id range [0, num_blocks)
 // is cut into kBins equal bins (ids outside it go to the last bin; the copy
@@ -1077,6 +1266,9 @@ __global__ void __launch_bounds__(kOrderThreads)
 }
 
 #define KVX_UNPAREN(...) __VA_ARGS__
+
+constexpr uint64_t kListMinPadding = 1u << 15;
+constexpr uint32_t kListTail = 2048;  // eight workgroups a compute unit
 
 // Whether a paged-attention scatter of tiles of at most 256 vectors runs them
 // on half as many threads with two vectors each. Twice as many of
@@ -1257,6 +1449,68 @@ hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, unit, part, cnt, packed, err);
   });
+}
+
+// Workgroups `first` and up of a list copy, `n` of them.
+template <bool kToPacked, bool kLoop>
+hipError_t launch_list_copy(const LayerPtrs& lp, const int32_t* bt, const ListBlock* blocks,
+                            const uint32_t* count, const ChunkGeom& cg, uint32_t first, uint32_t n,
+                            char* packed, int* err, int layout, int elem, hipStream_t stream) {
+  const SlabGeom& sg = cg.sg;
+  constexpr size_t hold = 0;
+  const dim3 grid(n);
+  if (cg.group > 1)
+    KVX_LAUNCH_GROUPS(copy_list_groups_kernel, (kToPacked, kLoop), cg.n16, cg.group, lp, bt, blocks,
+                      count, cg, first, n, packed, err);
+  else
+    KVX_DISPATCH(copy_list_kernel, (kToPacked, kLoop), lp, bt, blocks, count, cg, first, n, packed,
+                 err);
+  return hipGetLastError();
+}
+
+// The list's blocks counted and listed in scratch, then one copy over them.
+template <bool kToPacked>
+hipError_t launch_list(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_ref* refs,
+                       const ChunkGeom& cg, uint32_t* scratch, char* packed, int* err, int layout,
+                       int elem, hipStream_t stream) {
+  ListBlock* blocks = reinterpret_cast<ListBlock*>(scratch + 8);
+  const bool pair = kToPacked && cg.parts_shift < 32 && cg.group == 1;
+  hipLaunchKernelGGL(list_kernel, dim3((cg.n_chunks + kListChunks - 1) / kListChunks),
+                     dim3(kListThreads), 0, stream, refs, cg, pair ? 1u : 0u, blocks, scratch,
+                     err);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  e = launch_list_copy<kToPacked, false>(lp, bt, blocks, scratch, cg, 0, cg.list_grid, packed, err,
+                                         layout, elem, stream);
+  if (e == hipSuccess && layout == KVX_LAYOUT_PAGED_ATTN)
+    e = launch_list_copy<kToPacked, true>(lp, bt, blocks, scratch, cg, cg.list_grid,
+                                          std::min(cg.list_grid, kListTail), packed, err, layout,
+                                          elem, stream);
+  return e;
+}
+
+// Workgroups of a list copy without padding, or 0 where the padded copy is
+// taken: few padding workgroups by the table's length (a list's chunks hardly
+// ever share table entries) against the 12 us that the listing and its scratch
+// cost, as long as the card takes to dispatch 20,000 workgroups (65 us padded, 57
+// listed, with 38,000 of them); more units than a
+// launch takes; or a capturing stream, on which nothing is allocated.
+uint32_t list_grid(const ChunkGeom& g, hipStream_t stream) {
+  const uint64_t padded = (uint64_t)g.n_chunks * g.bpc, table = (uint64_t)g.table_len;
+  if (table >= padded || g.n_chunks > kListMaxChunks || padded > kListMaxBlocks) return 0;
+  const auto workgroups = [&](uint64_t blocks) {
+    return g.group > 1 ? (blocks * g.lr2 + g.group - 1) / g.group : blocks * g.lr2 * g.parts;
+  };
+  if (workgroups(padded) - workgroups(table) < kListMinPadding) return 0;
+  if (workgroups(padded) > 0x7FFFFFFF || workgroups(table) > kMaxWorkPerLaunch) return 0;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess ||
+      capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  // a multiple of the XCDs, so that a workgroup that goes round stays on its own
+  return (uint32_t)((workgroups(table) + kXcds - 1) / kXcds * kXcds);
 }
 
 DivU32 div_u32(uint32_t d) {
@@ -1463,7 +1717,7 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
                               const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
                               void* packed, int64_t packed_bytes, hipStream_t stream,
-                              int* err) {
+                              int* err, bool may_allocate) {
   if (n_chunks <= 0 || l1 <= l0) return KVX_OK;
   if (!err) return KVX_EHIP;
   const int64_t slab = (int64_t)cache->block_size * cache->num_kv_heads * cache->head_dim *
@@ -1477,7 +1731,7 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
     lp.p[2 * (l - l0)] = static_cast<char*>(cache->k[l]);
     lp.p[2 * (l - l0) + 1] = static_cast<char*>(cache->v[l]);
   }
-  ChunkGeom cg;
+  ChunkGeom cg = {};
   cg.upc = (uint32_t)upc;
   cg.bpc = (uint32_t)bpc;
   cg.lr2 = (uint32_t)(2 * (l1 - l0));
@@ -1495,10 +1749,31 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.slab = (uint64_t)slab;
   cg.packed_bytes = packed_bytes;
   cg.sg = slab_geom(cache, to_packed);
-  hipError_t e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, (char*)packed, err,
-                                                 layout, elem, stream)
-                           : launch_chunks<false>(lp, block_table, refs, cg, (char*)packed, err,
-                                                  layout, elem, stream);
+  cg.n_chunks = (uint32_t)n_chunks;
+  cg.lr2_div = div_u32(cg.lr2);
+  cg.list_grid = may_allocate ? list_grid(cg, stream) : 0;
+  char* pk = static_cast<char*>(packed);
+  hipError_t e;
+  uint32_t* scratch = nullptr;
+  if (cg.list_grid) {
+    // one entry per block the list can have, after the count
+    const size_t bytes = 32 + (size_t)n_chunks * bpc * sizeof(ListBlock);
+    if (hipMallocAsync((void**)&scratch, bytes, stream) != hipSuccess) {
+      (void)hipGetLastError();
+      scratch = nullptr;  // the padded copy needs none
+    }
+  }
+  if (scratch) {
+    e = to_packed ? launch_list<true>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
+                                      stream)
+                  : launch_list<false>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
+                                       stream);
+    const hipError_t ef = hipFreeAsync(scratch, stream);
+    if (e == hipSuccess) e = ef;
+  } else {
+    e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, pk, err, layout, elem, stream)
+                  : launch_chunks<false>(lp, block_table, refs, cg, pk, err, layout, elem, stream);
+  }
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
 

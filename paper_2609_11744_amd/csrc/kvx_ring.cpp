@@ -689,7 +689,7 @@ kvx_status launch_piece(kvx_ring* r, bool to_packed, const kvx::Piece& p, const 
                         uint8_t* dslot, hipStream_t stream) {
   return kvx::launch_copy_chunks(to_packed, &r->cache, p.l_begin, p.l_end, bt, r->plan.table_len,
                                  r->d_refs + p.ref_first, p.ref_count, r->chunk_tokens, dslot,
-                                 r->slot_bytes, stream, r->err_word);
+                                 r->slot_bytes, stream, r->err_word, false);
 }
 
 // ---- timeline (kvx_ring_set_trace) ----------------------------------------------

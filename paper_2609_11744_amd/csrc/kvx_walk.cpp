@@ -106,10 +106,15 @@ bool scatter_linear(int64_t n_blocks, int64_t slab, int layout, int32_t heads) {
 // least as fast on 11 of the 12 pairs) and 76.3 against 76.1 at 5,000; with
 // 4-block chunks the two were level (73.6 / 73.6), and destination order led
 // with 16 and 64 (74.6 against 71.8 and 75.0 against 70.8 at 2,048 blocks,
-// 76.9 against 71.9 at 5,000 with 16).
+// 76.9 against 71.9 at 5,000 with 16). A call over one layer keeps image
+// order: bucketing its ids and the scratch for them take 10 us, more than the
+// order gains there (32 KiB slabs in 16-block chunks, ordered / image order:
+// 1,024 blocks 30.9 / 24.7 us, 2,048 55.5 / 51.3, 4,096 102.6 / 96.2, 8,192
+// 194.5 / 188.6).
 bool scatter_in_destination_order(int64_t n_blocks, int64_t bpc, int64_t slab, int layout,
-                                  int32_t heads) {
-  return n_blocks >= kOrderedScatterMinBlocks && bpc > 1 && !small_rows(slab, layout, heads);
+                                  int32_t heads, int32_t layers) {
+  return n_blocks >= kOrderedScatterMinBlocks && bpc > 1 && layers > 1 &&
+         !small_rows(slab, layout, heads);
 }
 
 // Pairing for the ordered scatter of n_work work items (one launch) over
@@ -193,7 +198,7 @@ kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g
   }
   w->linear = scatter_linear(g.n_blocks, g.slab, cache->layout, cache->num_kv_heads);
   w->ordered = scatter_in_destination_order(g.n_blocks, g.bpc, g.slab, cache->layout,
-                                            cache->num_kv_heads);
+                                            cache->num_kv_heads, g.lr);
   if (w->ordered)
     w->pair_shift = scatter_pairing(std::max(n_work, (uint64_t)g.n_units * w->pieces), pair_parts,
                                     n_slices, (uint32_t)g.bpc, (uint64_t)g.slab);

@@ -1,0 +1,153 @@
+"""Chunk lists most of whose chunks are short, copied without padding: every
+layout and grouping, more chunks than one listing workgroup takes, chunks whose
+slices lie 2 MiB apart (the paired gather), chunks that share table entries (more
+blocks than the table has: workgroups go round again), bad references and bad
+block ids, and the same list while a stream is capturing (the padded copy).
+Everything is compared whole with the oracle."""
+import numpy as np
+import pytest
+
+import kvsynth
+import oracle
+from kvtest_util import Filled, device_cache, first_mismatch, host_mirror, seeded_ids, to_host
+
+torch = pytest.importorskip("torch")
+import paper_2609_11744_amd as kvx  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NHD, HND, PA = oracle.LAYOUT_NHD, oracle.LAYOUT_HND, oracle.LAYOUT_PAGED_ATTN
+
+CASES = [
+    # (layout, layers, block, heads, dim, elem, blocks per chunk, chunk lengths)
+    (NHD, 8, 16, 2, 128, 2, 64, [1, 64, 3, 32, 2, 64, 5, 1] + [2] * 40),   # 8 KiB: D = 4, 8
+    (NHD, 8, 16, 1, 64, 2, 64, [3, 1, 2] * 50),                            # 2 KiB, 150 chunks
+    (NHD, 8, 8, 1, 64, 1, 200, [7, 1, 4] * 30),                            # 512 bytes
+    (NHD, 9, 5, 3, 56, 2, 64, [1, 2, 64, 9] * 12),                         # 1,680 bytes
+    (NHD, 9, 16, 3, 80, 2, 64, [2, 5, 1] * 16),                            # 7,680 bytes
+    (HND, 8, 16, 2, 128, 2, 64, [1, 33, 2] * 16),
+    (HND, 8, 8, 2, 64, 1, 128, [5, 1, 17] * 12),                           # 1 KiB
+    (PA, 8, 16, 8, 128, 1, 64, [1, 4, 2] * 6),                             # two heads a tile
+    (PA, 8, 16, 1, 128, 2, 64, [1, 32, 3] * 16),                           # one head a tile
+    (PA, 8, 8, 1, 64, 2, 200, [3, 1, 11] * 12),                            # 1 KiB
+]
+
+
+def _bt(ids):
+    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(DEV)
+
+
+def _setup(case, NB, seed):
+    layout, L, bs, h, d, e, _, _ = case
+    s = oracle.Shape(L, NB, bs, h, d, e, layout)
+    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
+    return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
+
+
+def _refs(lengths, per_block, gap=16):
+    refs, at, off = [], 0, 64
+    for m in lengths:
+        refs.append((off, at, m))
+        at, off = at + m, off + m * per_block + gap
+    return refs, at, off
+
+
+def _same_cache(cache, mirror, L):
+    torch.cuda.synchronize()
+    for l in range(L):
+        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
+        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
+
+
+def _want(s, mirror, L, ids, refs, size, bs):
+    want = np.full(size, 0xA5, np.uint8)
+    for o, a, m in refs:
+        img = oracle.gather(s, *mirror, 0, L, ids[a:a + m], m * bs)
+        want[o:o + img.size] = img
+    return want
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"r{i}" for i in range(len(CASES))])
+def test_ragged_lists_bit_exact(case):
+    _, L, bs, _, _, _, bpc, lengths = case
+    n = sum(lengths)
+    s, cache, mirror = _setup(case, 2 * n + 3, 900)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    refs, table_len, size = _refs(lengths, per_block)
+    src, dst_ids = seeded_ids(900, 2 * n + 3, n, n)
+    rd = kvx.chunk_refs(refs, DEV)
+    out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(src), table_len, rd, len(refs), bpc * bs, out)
+    kvx.kvx_check()
+    want = _want(s, mirror, L, src, refs, size, bs)
+    assert first_mismatch(to_host(out), want) is None
+    kvx.kvx_scatter_chunks(cache, 0, L, _bt(dst_ids), table_len, rd, len(refs), bpc * bs, out)
+    kvx.kvx_check()
+    for o, a, m in refs:
+        oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, want[o:o + m * per_block])
+    _same_cache(cache, mirror, L)
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[2], CASES[7], CASES[9]],
+                         ids=["parts", "wave", "lane", "tile", "paged"])
+def test_ragged_lists_sharing_entries_bad_refs_and_ids(case):
+    _, L, bs, _, _, _, bpc, _ = case
+    n, NB = 23, 60
+    s, cache, mirror = _setup(case, NB, 910)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    (ids,) = seeded_ids(910, NB, n)
+    rng = np.random.default_rng(7)
+    refs, off = [], 0
+    for c in range(70):  # 70 chunks over 23 entries: about nine times the table's blocks
+        m = int(rng.integers(1, 6))
+        refs.append((off, int(rng.integers(0, n - m + 1)), m))
+        off += m * per_block
+    bad = {5: (refs[5][0] + 8, refs[5][1], refs[5][2]), 64: (refs[64][0], n - 1, 4)}
+    given = [bad.get(c, r) for c, r in enumerate(refs)]
+    out = torch.full((off,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids), n, kvx.chunk_refs(given, DEV), len(refs),
+                          bpc * bs, out)
+    with pytest.raises(kvx.KvxError) as e:
+        kvx.kvx_check()
+    assert e.value.status == kvx.KVX_EINVAL
+    good = [r for c, r in enumerate(refs) if c not in bad]
+    want = _want(s, mirror, L, ids, good, off, bs)
+    assert first_mismatch(to_host(out), want) is None
+    # a bad block id: its slabs alone are left as they are
+    ids2 = ids.copy()
+    ids2[4] = NB
+    lengths = [1] * n
+    one, table_len, size = _refs(lengths, per_block)
+    out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids2), n, kvx.chunk_refs(one * 3, DEV), 3 * n,
+                          bpc * bs, out)
+    with pytest.raises(kvx.KvxError) as e:
+        kvx.kvx_check()
+    assert e.value.status == kvx.KVX_EBADBLOCK
+    want = _want(s, mirror, L, ids, [r for r in one if r[1] != 4], size, bs)
+    assert first_mismatch(to_host(out), want) is None
+
+
+def test_ragged_list_under_capture_replays_bit_exact():
+    case = CASES[0]
+    _, L, bs, _, _, _, bpc, lengths = case
+    n = sum(lengths)
+    s, cache, mirror = _setup(case, 2 * n + 3, 920)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    refs, table_len, size = _refs(lengths, per_block)
+    (src,) = seeded_ids(920, 2 * n + 3, n)
+    rd, bt = kvx.chunk_refs(refs, DEV), _bt(src)
+    out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, bt, table_len, rd, len(refs), bpc * bs, out)
+    kvx.kvx_check()
+    want = _want(s, mirror, L, src, refs, size, bs)
+    assert first_mismatch(to_host(out), want) is None
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        kvx.kvx_gather_chunks(cache, 0, L, bt, table_len, rd, len(refs), bpc * bs, out)
+    for rep in range(3):
+        out.fill_(0xA5)
+        torch.cuda.synchronize()
+        g.replay()
+        kvx.kvx_check()
+        assert first_mismatch(to_host(out), want) is None, f"replay {rep}"
