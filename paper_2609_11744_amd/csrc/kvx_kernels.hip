@@ -1717,7 +1717,7 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
                               const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
                               void* packed, int64_t packed_bytes, hipStream_t stream,
-                              int* err, bool may_allocate) {
+                              int* err) {
   if (n_chunks <= 0 || l1 <= l0) return KVX_OK;
   if (!err) return KVX_EHIP;
   const int64_t slab = (int64_t)cache->block_size * cache->num_kv_heads * cache->head_dim *
@@ -1751,7 +1751,7 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.sg = slab_geom(cache, to_packed);
   cg.n_chunks = (uint32_t)n_chunks;
   cg.lr2_div = div_u32(cg.lr2);
-  cg.list_grid = may_allocate ? list_grid(cg, stream) : 0;
+  cg.list_grid = list_grid(cg, stream);
   char* pk = static_cast<char*>(packed);
   hipError_t e;
   uint32_t* scratch = nullptr;
