@@ -162,14 +162,15 @@ kvx_status kvx_scatter_blocks(const kvx_cache* cache, int32_t l0, int32_t l1,
  * or where pieces are small several, or a share of a large one. A scatter of
  * 1,024 blocks or more over more than one layer, in chunks of more than one
  * block, runs in ascending destination order (ordered = 1; block ids bucketed
- * by a small kernel first), except with slabs of at most 8 KiB in the default layout (or a reordering
- * layout with one KV head): those, like every smaller scatter, walk the packed
- * image in order, with linear = 1 (slabs that divide 4 KiB or are a multiple
- * of it) when the b-th workgroup moves the b-th share of the image rather than
- * each XCD taking one contiguous range. pair_slices = D > 0: slices D apart,
- * whose runs sit 2 MiB apart in a packed chunk, are moved together (the
- * gather's paired walk, or an ordered scatter's two fronts per XCD: fronts =
- * 2). For an empty call every field is 0. KVX_EINVAL for the arguments the copy
+ * by a small kernel first), except with slabs of at most 8 KiB in the default
+ * layout (or a reordering layout with one KV head), or of at most 2 KiB in any:
+ * those, like every smaller scatter, walk the packed image in order, with
+ * linear = 1 (slabs that divide 4 KiB or are a multiple of it) when the b-th
+ * workgroup moves the b-th share of the image rather than each XCD taking one
+ * contiguous range. pair_slices = D > 0: slices D apart, whose runs sit 2 MiB
+ * apart in a packed chunk, are moved together (the gather's paired walk, or an
+ * ordered scatter's two fronts per XCD: fronts = 2). For an empty call every
+ * field is 0. KVX_EINVAL for the arguments the copy
  * calls reject on the host (except pointers). */
 typedef struct kvx_walk {
   int64_t work_items;

@@ -1040,8 +1040,11 @@ __device__ __forceinline__ void move_grouped(const Place& p, uint32_t w, const S
 }
 
 // Paged attention: each slab of the group has an LDS image of its own and is one
-// tile (gh = heads, dw = v16). Called by every thread of the workgroup.
-template <bool kToPacked, int kElem>
+// tile (gh = heads, dw = v16). Called by every thread of the workgroup. 1 GiB of
+// 2 KiB slabs, 8-bit, one head, gather / scatter: 516 / 552 us with a slab per
+// workgroup, 404 / 411 grouped with a unit decoded by every lane, 370 / 372 with
+// one per wave; 512-byte slabs 1480 / 1526 -> 575 / 513 us (by lane).
+template <bool kToPacked, int kElem, bool kWave>
 __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, uint32_t w,
                                                    const SlabGeom& g) {
   typedef typename std::conditional<
@@ -1063,7 +1066,7 @@ __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, u
     v = v_bytes<kToPacked>(w, g, image, &w);
   else
     v = v_elements<kToPacked, false, E>(w, g, image);
-  store_grouped<false>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
+  store_grouped<kWave>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
 }
 
 // Unit u of a grouped call in image order, or (kOrdered) slice by slice in the
@@ -1115,7 +1118,7 @@ __global__ void __launch_bounds__(kPartThreads)
   if (i < g.group && u < g.n_units)
     p = place_unit<kToPacked, kOrdered>(layers, block_table, g, u, order, packed, err, w == 0);
   if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN)
-    move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+    move_grouped_paged<kToPacked, kElem, kWave>(p, i, w, g.sg);
   else if (p.ok)
     move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
@@ -1161,7 +1164,7 @@ __global__ void __launch_bounds__(kPartThreads)
   if (i < g.group && u < g.n_units)
     p = place_chunk_unit<kToPacked>(layers, block_table, refs, g, u, packed, err, w == 0);
   if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN)
-    move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+    move_grouped_paged<kToPacked, kElem, kWave>(p, i, w, g.sg);
   else if (p.ok)
     move_grouped<kToPacked, kLayout, kWave>(p, w, g.sg);
 }
@@ -1196,7 +1199,7 @@ __global__ void __launch_bounds__(kPartThreads)
       p.kv = lk & 1;
     }
     if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN) {
-      move_grouped_paged<kToPacked, kElem>(p, i, w, g.sg);
+      move_grouped_paged<kToPacked, kElem, kWave>(p, i, w, g.sg);
       if (!kAgain) return;
       __syncthreads();  // before the LDS images are reused
     } else if (p.ok) {
@@ -1391,6 +1394,14 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
   hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, WAVE>), grid,           \
                      dim3(kPartThreads), LDS, stream, __VA_ARGS__)
 
+#define KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, ELEM, ...)                                   \
+  do {                                                                                 \
+    if (wave)                                                                          \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, true, lds, __VA_ARGS__); \
+    else                                                                               \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, false, lds, __VA_ARGS__); \
+  } while (0)
+
 #define KVX_LAUNCH_GROUPS(KERNEL, PREFIX, N16, GROUP, ...)                                  \
   do {                                                                                 \
     const bool wave = (N16) % 64 == 0;                                                 \
@@ -1404,13 +1415,13 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
     else if (layout == KVX_LAYOUT_HND)                                                 \
       KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, false, hold, __VA_ARGS__);    \
     else if (elem == 1)                                                                \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, false, lds, __VA_ARGS__); \
+      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 1, __VA_ARGS__); \
     else if (elem == 2)                                                                \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 2, false, lds, __VA_ARGS__); \
+      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 2, __VA_ARGS__); \
     else if (elem == 4)                                                                \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 4, false, lds, __VA_ARGS__); \
+      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 4, __VA_ARGS__); \
     else                                                                               \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, false, lds, __VA_ARGS__); \
+      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 8, __VA_ARGS__); \
   } while (0)
 
 template <bool kToPacked, bool kOrdered>

@@ -87,8 +87,13 @@ namespace {
 // 474 / 409 / 393, 3,840 bytes 409 / 387 / 395, 5,120 bytes 483 / 392 / 383,
 // 6 KiB 423 / 388 / 386, 7 KiB 398 / 388 / 386; 8 KiB 364 / 384 / 376. Grouped
 // ones the same: 1,920 bytes 414 / 407 / 399 us, 1,280 bytes 407 / 412 / 400.
+// Slabs of several heads in a reordering layout join them where they are grouped
+// (2 KiB, two heads of 64 dims 8-bit, ordered / linear: HND 415 / 387 us, paged
+// attention 400 / 370; 1,920 bytes ordered / image order 430 / 418, 543 / 450;
+// eight-token blocks of two such heads lost 2 to 5 % in the latter).
 bool small_rows(int64_t slab, int layout, int32_t heads) {
-  return slab <= 8192 && (layout == KVX_LAYOUT_NHD || heads == 1);
+  return slab <= 16 * (int64_t)kGroupMaxVectors ||
+         (slab <= 8192 && (layout == KVX_LAYOUT_NHD || heads == 1));
 }
 
 bool scatter_linear(int64_t n_blocks, int64_t slab, int layout, int32_t heads) {
