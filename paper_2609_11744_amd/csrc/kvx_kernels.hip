@@ -3,8 +3,8 @@
 //
 // The work is pure data movement, bound by HBM bandwidth, so the kernels use
 // no MFMA. With the default cache layout every slab is contiguous and in the
-// same order on both sides, so nothing is transposed and no LDS is used; the
-// other cache layouts move a slab head by head (see move_head).
+// same order on both sides, so nothing is transposed and no LDS is used; of the
+// other cache layouts only paged attention goes through LDS (see move_tile).
 // A unit is a slab (layer, K|V, block) of `slab` bytes. With the default
 // layout one workgroup moves one part of a unit: 256 threads, one 16-byte
 // vector each, so a part is 4 KiB (a 32 KiB slab is 8 parts; the last part of
@@ -13,7 +13,8 @@
 // with several vectors per thread in fewer, longer ones (contiguous 4 GiB:
 // 83 % of peak against 77.5 % at 1024 threads x 2 vectors; the 80k gather
 // pattern 76.7 % against 73.6 %); persistent grids that loop over units
-// measured lower still. The other layouts move a whole slab per workgroup.
+// measured lower still. HND moves the same pieces, paged attention tiles of about
+// that size; slabs of at most 2 KiB share a workgroup (copy_unit_groups_kernel).
 //   * the unit's decode (chunk, layer, K|V, block, part) and its block-table
 //     read depend on blockIdx only, so they run on the scalar unit once per
 //     workgroup;
@@ -37,9 +38,9 @@
 // less than unordered writes. The exceptions measured faster in image order:
 // a chunk of one block (each chunk is then one sequential read, and the
 // writes go to one destination block of every layer in turn;
-// scatter_in_destination_order in kvx_walk.cpp), and slabs of at most 8 KiB,
-// walked with no XCD ranges so that the whole chip reads the packed image
-// front to back (scatter_linear).
+// scatter_in_destination_order in kvx_walk.cpp), a call over one layer, and
+// slabs of at most 8 KiB, most of them walked with no XCD ranges so that the
+// whole chip reads the packed image front to back (scatter_linear).
 //
 // Pairing at 2 MiB. Where a layer|K|V slice's run in a packed chunk (blocks
 // per chunk x slab) times a power of two D is 2 MiB, both directions can move
@@ -575,14 +576,14 @@ __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
 
 template <bool kToPacked>
 __device__ __forceinline__ v4u v_bytes(uint32_t w, const SlabGeom& g, const unsigned char* image,
-                                       uint32_t* at) {
+                                       uint32_t row, uint32_t* at) {
   const uint32_t k = w >> 4, l = w & 15u;
   uint32_t tg, dv, h, first, step;
   if (kToPacked) {  // rows: dims 16 dv + i; columns: tokens 16 tg ..
     h = divmod(divmod(k, g.dwd, dv), g.bs16, tg);
     first = h * g.np.d + dv * g.bs.d + (l >> 1) * g.bs16.d + tg;
     step = 8 * g.bs16.d;
-    *at = (16 * tg + l) * g.prow + h * g.dw + dv;
+    *at = (16 * tg + l) * row + h * g.dw + dv;
   } else {  // rows: tokens 16 tg + i; columns: dims 16 dv ..
     h = divmod(divmod(k, g.bs16, tg), g.dwd, dv);
     first = (16 * tg + (l >> 1)) * g.row.d + h * g.dw + dv;
@@ -610,12 +611,38 @@ __device__ __forceinline__ void v_bytes_out(v4u* __restrict__ dst, const SlabGeo
   for (int q = 0; q < V; ++q) {
     const uint32_t w = threadIdx.x + q * T;
     ok[q] = w < tile.heads * g.np.d;  // the same for the 16 lanes of a group
-    if (ok[q]) r[q] = v_bytes<kToPacked>(w, g, kvx_lds, &at[q]);
+    if (ok[q]) r[q] = v_bytes<kToPacked>(w, g, kvx_lds, g.prow, &at[q]);
   }
   const auto out = stream_dst(dst, tile_dst_bytes<kToPacked>(g));
 #pragma unroll
   for (int q = 0; q < V; ++q)
     if (ok[q]) store_stream(out, at[q], r[q]);
+}
+
+// The same for a gather whose rows are not whole 64-byte runs of four lane
+// groups: a group's 16 bytes of 16 tokens would be stored as parts of lines. The
+// vectors go back to the LDS in packed order first and leave as whole rows.
+// 3 heads of 80 dims, 1 GiB: 651 us stored directly, 388 by elements, 363
+// this way; 5 heads of 96 dims 623, 375, 367 us.
+template <int T, int V>
+__device__ __forceinline__ void v_bytes_rows_out(v4u* __restrict__ dst, const SlabGeom& g,
+                                                 const Tile& tile) {
+  v4u* lds = reinterpret_cast<v4u*>(kvx_lds);
+  v4u r[V];
+  uint32_t at[V];
+  bool ok[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    const uint32_t w = threadIdx.x + q * T;
+    ok[q] = w < tile.heads * g.np.d;
+    if (ok[q]) r[q] = v_bytes<true>(w, g, kvx_lds, g.row.d, &at[q]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < V; ++q)
+    if (ok[q]) lds[at[q]] = r[q];
+  __syncthreads();
+  stage_out<true, false, T, V>(dst, g, tile, [&](uint32_t w) { return lds[w]; });
 }
 
 // One tile of a paged-attention slab (pv, pk: the slab's first vector on the
@@ -638,6 +665,8 @@ __device__ __forceinline__ void move_tile(v4u* pv, v4u* pk, const SlabGeom& g, u
     stage_out<kToPacked, kOne, T, V>(dst, g, tile, [&](uint32_t w) {
       return lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, kOne>(w, g), g)];
     });
+  else if (kElem == 1 && kToPacked && g.v_bytes == 2)
+    v_bytes_rows_out<T, V>(dst, g, tile);
   else if (kElem == 1 && g.v_bytes)
     v_bytes_out<kToPacked, T, V>(dst, g, tile);
   else if (kToPacked && kElem == 2 && g.v_pairs)
@@ -1058,12 +1087,24 @@ __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, u
     lds[lds_slot<kToPacked, kElem>(w, g)] = __builtin_nontemporal_load(
         reinterpret_cast<const v4u*>(kToPacked ? p.paged : p.packed) + w);
   __syncthreads();
-  if (!p.ok) return;
   v4u v;
+  if (kElem == 1 && kToPacked && g.v_bytes == 2) {  // as v_bytes_rows_out; uniform
+    const bool turn = p.ok && p.kv != 0;
+    uint32_t at;
+    if (turn) v = v_bytes<true>(w, g, image, g.row.d, &at);
+    else if (p.ok) v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
+    __syncthreads();
+    if (turn) lds[at] = v;
+    __syncthreads();
+    if (turn) v = lds[w];
+    if (p.ok) store_grouped<kWave>(p.base, p.packed, g.n16.d, w, v);
+    return;
+  }
+  if (!p.ok) return;
   if (p.kv == 0)
     v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
   else if (kElem == 1 && g.v_bytes)
-    v = v_bytes<kToPacked>(w, g, image, &w);
+    v = v_bytes<kToPacked>(w, g, image, g.prow, &w);
   else
     v = v_elements<kToPacked, false, E>(w, g, image);
   store_grouped<kWave>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
@@ -1271,6 +1312,7 @@ __global__ void __launch_bounds__(kOrderThreads)
 #define KVX_UNPAREN(...) __VA_ARGS__
 
 constexpr uint64_t kListMinPadding = 1u << 15;
+constexpr uint64_t kListMinWork = 1u << 13;
 constexpr uint32_t kListTail = 2048;  // eight workgroups a compute unit
 
 // Whether a paged-attention scatter of tiles of at most 256 vectors runs them
@@ -1505,14 +1547,19 @@ hipError_t launch_list(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_r
 // ever share table entries) against the 12 us that the listing and its scratch
 // cost, as long as the card takes to dispatch 20,000 workgroups (65 us padded, 57
 // listed, with 38,000 of them); more units than a
-// launch takes; or a capturing stream, on which nothing is allocated.
+// launch takes; or a capturing stream, on which nothing is allocated. Nor lists
+// of less than 32 MiB or so, which run in less than the 24 us of host time that
+// the scratch takes (17 MiB in 6 chunks of 1 or 2 of 16 blocks: 22 us
+// padded, 26 listed).
 uint32_t list_grid(const ChunkGeom& g, hipStream_t stream) {
   const uint64_t padded = (uint64_t)g.n_chunks * g.bpc, table = (uint64_t)g.table_len;
   if (table >= padded || g.n_chunks > kListMaxChunks || padded > kListMaxBlocks) return 0;
   const auto workgroups = [&](uint64_t blocks) {
     return g.group > 1 ? (blocks * g.lr2 + g.group - 1) / g.group : blocks * g.lr2 * g.parts;
   };
-  if (workgroups(padded) - workgroups(table) < kListMinPadding) return 0;
+  if (workgroups(padded) - workgroups(table) < kListMinPadding ||
+      workgroups(table) < kListMinWork)
+    return 0;
   if (workgroups(padded) > 0x7FFFFFFF || workgroups(table) > kMaxWorkPerLaunch) return 0;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &capture) != hipSuccess ||
@@ -1591,10 +1638,8 @@ SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   // V of 2-byte words as row pairs in a gather: token pairs, so an even
   // block size (v_pairs_gather says why not in a scatter)
   sg.v_pairs = c->elem_bytes == 2 && to_packed && bs % 2 == 0 ? 1u : 0u;
-  // transpose reads: a gather's 16-lane groups store 16 bytes of 16 tokens each,
-  // so four neighbouring groups must make up at least 64 bytes of every token
-  // (3 heads of 80 dims, five vectors a row: 651 us, by elements 388)
-  sg.v_bytes = c->elem_bytes == 1 && bs % 16 == 0 && (!to_packed || sg.dw % 4 == 0) ? 1u : 0u;
+  // transpose reads; 2: a gather's rows are not whole 64-byte runs (v_bytes_rows_out)
+  sg.v_bytes = c->elem_bytes != 1 || bs % 16 != 0 ? 0u : to_packed && sg.dw % 4 != 0 ? 2u : 1u;
   sg.bs16 = fast_div(bs / 16);
   const uint32_t stride = to_packed ? bs : sg.row.d;
   sg.swz = 4;

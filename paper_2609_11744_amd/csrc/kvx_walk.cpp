@@ -38,7 +38,7 @@ TileShape paged_tile(uint32_t block_size, uint32_t heads, uint32_t v16) {
     const uint32_t tiles = (heads + g - 1) / g;
     float f = (float)(heads * nh) / (float)(tiles * v * kPartThreads);
     if (v > 1) f *= v == 2 ? 0.96f : 0.93f;
-    if (g < heads && g * v16 % kLine != 0) f *= 0.7f;
+    if (g < heads && g * v16 % kLine != 0) f *= 0.5f;
     if (f > score) score = f, best = {g, v16};
   }
   for (uint32_t w = kLine; w < v16; w += kLine)

@@ -19,18 +19,25 @@ DEV = "cuda:0"
 NHD, HND, PA = oracle.LAYOUT_NHD, oracle.LAYOUT_HND, oracle.LAYOUT_PAGED_ATTN
 
 CASES = [
-    # (layout, layers, block, heads, dim, elem, blocks per chunk, chunk lengths)
-    (NHD, 8, 16, 2, 128, 2, 64, [1, 64, 3, 32, 2, 64, 5, 1] + [2] * 40),   # 8 KiB: D = 4, 8
-    (NHD, 8, 16, 1, 64, 2, 64, [3, 1, 2] * 50),                            # 2 KiB, 150 chunks
-    (NHD, 8, 8, 1, 64, 1, 200, [7, 1, 4] * 30),                            # 512 bytes
-    (NHD, 9, 5, 3, 56, 2, 64, [1, 2, 64, 9] * 12),                         # 1,680 bytes
-    (NHD, 9, 16, 3, 80, 2, 64, [2, 5, 1] * 16),                            # 7,680 bytes
-    (HND, 8, 16, 2, 128, 2, 64, [1, 33, 2] * 16),
-    (HND, 8, 8, 2, 64, 1, 128, [5, 1, 17] * 12),                           # 1 KiB
-    (PA, 8, 16, 8, 128, 1, 64, [1, 4, 2] * 6),                             # two heads a tile
-    (PA, 8, 16, 1, 128, 2, 64, [1, 32, 3] * 16),                           # one head a tile
-    (PA, 8, 8, 1, 64, 2, 200, [3, 1, 11] * 12),                            # 1 KiB
+    # (layout, layers, block, heads, dim, elem, blocks per chunk, chunk lengths, slabs' workgroups)
+    (NHD, 16, 16, 2, 128, 2, 64, [1, 64, 3, 32, 2, 64, 5, 1] + [2] * 40, 2),  # 8 KiB: D = 4, 8
+    (NHD, 32, 16, 1, 64, 2, 64, [3, 1, 2] * 50, 1 / 2),                       # 2 KiB, 150 chunks
+    (NHD, 32, 8, 1, 64, 1, 200, [7, 1, 4] * 90, 1 / 8),                       # 512 bytes
+    (NHD, 17, 5, 3, 56, 2, 64, [1, 2, 64, 9] * 12, 1 / 2),                    # 1,680 bytes
+    (NHD, 17, 16, 3, 80, 2, 64, [2, 5, 1] * 16, 2),                           # 7,680 bytes
+    (HND, 16, 16, 2, 128, 2, 64, [1, 33, 2] * 5, 2),
+    (HND, 32, 8, 2, 64, 1, 128, [5, 1, 17] * 23, 1 / 4),                      # 1 KiB
+    (PA, 8, 16, 8, 128, 1, 64, [1, 4, 2] * 19, 4),                            # two heads a tile
+    (PA, 16, 16, 1, 128, 2, 64, [1, 32, 3] * 8, 1),                           # one head a tile
+    (PA, 32, 8, 1, 64, 2, 200, [3, 1, 11] * 35, 1 / 4),                       # 1 KiB
 ]
+
+
+def _listed(case, table_len, n_chunks):
+    """The list is copied without padding: enough work, and enough padding."""
+    work = table_len * 2 * case[1] * case[8]
+    padded = n_chunks * case[6] * 2 * case[1] * case[8]
+    return work >= 1 << 13 and padded - work >= 1 << 15
 
 
 def _bt(ids):
@@ -38,7 +45,7 @@ def _bt(ids):
 
 
 def _setup(case, NB, seed):
-    layout, L, bs, h, d, e, _, _ = case
+    layout, L, bs, h, d, e = case[:6]
     s = oracle.Shape(L, NB, bs, h, d, e, layout)
     fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
     return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
@@ -69,8 +76,9 @@ def _want(s, mirror, L, ids, refs, size, bs):
 
 @pytest.mark.parametrize("case", CASES, ids=[f"r{i}" for i in range(len(CASES))])
 def test_ragged_lists_bit_exact(case):
-    _, L, bs, _, _, _, bpc, lengths = case
+    _, L, bs, _, _, _, bpc, lengths, _ = case
     n = sum(lengths)
+    assert _listed(case, n, len(lengths))
     s, cache, mirror = _setup(case, 2 * n + 3, 900)
     per_block = oracle.packed_bytes(s, 0, L, 1)
     refs, table_len, size = _refs(lengths, per_block)
@@ -91,17 +99,19 @@ def test_ragged_lists_bit_exact(case):
 @pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[2], CASES[7], CASES[9]],
                          ids=["parts", "wave", "lane", "tile", "paged"])
 def test_ragged_lists_sharing_entries_bad_refs_and_ids(case):
-    _, L, bs, _, _, _, bpc, _ = case
-    n, NB = 23, 60
+    _, L, bs, _, _, _, bpc, _, per_slab = case
+    n = int(8192 / (2 * L * per_slab)) + 3
+    NB = n + 9
     s, cache, mirror = _setup(case, NB, 910)
     per_block = oracle.packed_bytes(s, 0, L, 1)
     (ids,) = seeded_ids(910, NB, n)
     rng = np.random.default_rng(7)
     refs, off = [], 0
-    for c in range(70):  # 70 chunks over 23 entries: about nine times the table's blocks
-        m = int(rng.integers(1, 6))
+    for c in range(max(70, n // 2)):  # more blocks than the table has
+        m = int(rng.integers(1, 8))
         refs.append((off, int(rng.integers(0, n - m + 1)), m))
         off += m * per_block
+    assert _listed(case, n, len(refs)) and sum(r[2] for r in refs) > 1.2 * n
     bad = {5: (refs[5][0] + 8, refs[5][1], refs[5][2]), 64: (refs[64][0], n - 1, 4)}
     given = [bad.get(c, r) for c, r in enumerate(refs)]
     out = torch.full((off,), 0xA5, dtype=torch.uint8, device=DEV)
@@ -116,21 +126,19 @@ def test_ragged_lists_sharing_entries_bad_refs_and_ids(case):
     # a bad block id: its slabs alone are left as they are
     ids2 = ids.copy()
     ids2[4] = NB
-    lengths = [1] * n
-    one, table_len, size = _refs(lengths, per_block)
+    single, _, size = _refs([1] * n, per_block)
     out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
-    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids2), n, kvx.chunk_refs(one * 3, DEV), 3 * n,
-                          bpc * bs, out)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids2), n, kvx.chunk_refs(single, DEV), n, bpc * bs, out)
     with pytest.raises(kvx.KvxError) as e:
         kvx.kvx_check()
     assert e.value.status == kvx.KVX_EBADBLOCK
-    want = _want(s, mirror, L, ids, [r for r in one if r[1] != 4], size, bs)
+    want = _want(s, mirror, L, ids, [r for r in single if r[1] != 4], size, bs)
     assert first_mismatch(to_host(out), want) is None
 
 
 def test_ragged_list_under_capture_replays_bit_exact():
     case = CASES[0]
-    _, L, bs, _, _, _, bpc, lengths = case
+    _, L, bs, _, _, _, bpc, lengths, _ = case
     n = sum(lengths)
     s, cache, mirror = _setup(case, 2 * n + 3, 920)
     per_block = oracle.packed_bytes(s, 0, L, 1)
