@@ -336,7 +336,8 @@ __device__ __forceinline__ void move_rows(const v4u* __restrict__ src, v4u* __re
   const uint32_t w = part * g.piece + threadIdx.x;
   const uint32_t end = (part + 1) * g.piece;
   const auto out = stream_dst(dst, n16 * 16u);
-  if (w < (end < n16 ? end : n16)) store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
+  if (w < (end < n16 ? end : n16))
+    store_stream(out, w, __builtin_nontemporal_load(src + hnd_source(w, g)));
 }
 
 // A workgroup's tile of a paged-attention slab: its first vector on the cache
@@ -1110,28 +1111,17 @@ __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, u
   store_grouped<kWave>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
 }
 
-// Unit u of a grouped call in image order, or (kOrdered) slice by slice in the
-// order's ascending destinations.
-template <bool kToPacked, bool kOrdered>
+// Unit u of a grouped call, in image order (slabs this small take no other:
+// small_rows, kvx_walk.cpp).
+template <bool kToPacked>
 __device__ __forceinline__ Place place_unit(const LayerPtrs& layers, const int32_t* block_table,
-                                            const UnitGeom& g, uint32_t u, const OrderEntry* order,
-                                            char* packed, int* err, bool report) {
-  uint32_t lk;
-  int32_t id;
-  if (kOrdered) {
-    lk = divu(u, g.nb_div);
-    const OrderEntry e = order[u - lk * g.n_blocks];
-    const uint32_t c = divu(e.index, g.bpc_div), first = c * g.bpc;
-    const uint32_t left = g.n_blocks - first;
-    id = e.id;
-    u = c * g.units_per_chunk + lk * (left < g.bpc ? left : g.bpc) + e.index - first;
-  } else {
-    const uint32_t c = divu(u, g.upc_div), first = c * g.bpc;
-    const uint32_t r = u - c * g.units_per_chunk, left = g.n_blocks - first;
-    const bool full = left >= g.bpc;
-    lk = divu(r, full ? g.bpc_div : g.last_div);
-    id = block_table[first + r - lk * (full ? g.bpc : left)];
-  }
+                                            const UnitGeom& g, uint32_t u, char* packed, int* err,
+                                            bool report) {
+  const uint32_t c = divu(u, g.upc_div), first = c * g.bpc;
+  const uint32_t r = u - c * g.units_per_chunk, left = g.n_blocks - first;
+  const bool full = left >= g.bpc;
+  const uint32_t lk = divu(r, full ? g.bpc_div : g.last_div);
+  const int32_t id = block_table[first + r - lk * (full ? g.bpc : left)];
   char* layer = layers.p[lk];
   Place p;
   p.ok = (uint32_t)id < g.num_blocks;
@@ -1144,11 +1134,10 @@ __device__ __forceinline__ Place place_unit(const LayerPtrs& layers, const int32
 }
 
 // kElem: the word size with paged attention, else 0.
-template <bool kToPacked, bool kOrdered, int kLayout, int kElem, bool kWave>
+template <bool kToPacked, int kLayout, int kElem, bool kWave>
 __global__ void __launch_bounds__(kPartThreads)
     copy_unit_groups_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table, UnitGeom g,
-                            uint32_t group_base, uint32_t group_count,
-                            const OrderEntry* __restrict__ order, char* __restrict__ packed,
+                            uint32_t group_base, uint32_t group_count, char* __restrict__ packed,
                             int* __restrict__ err) {
   uint32_t w;
   const uint32_t i = grouped_unit<kWave>(g.sg, &w);
@@ -1157,7 +1146,7 @@ __global__ void __launch_bounds__(kPartThreads)
                          g.group + i;
   Place p = {};
   if (i < g.group && u < g.n_units)
-    p = place_unit<kToPacked, kOrdered>(layers, block_table, g, u, order, packed, err, w == 0);
+    p = place_unit<kToPacked>(layers, block_table, g, u, packed, err, w == 0);
   if constexpr (kLayout == KVX_LAYOUT_PAGED_ATTN)
     move_grouped_paged<kToPacked, kElem, kWave>(p, i, w, g.sg);
   else if (p.ok)
@@ -1473,12 +1462,15 @@ hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
   const SlabGeom& sg = ug.sg;
   const size_t hold =
       !kToPacked && ug.linear_walk && ug.n16 >= kHeldMinVectors ? kLinearScatterLds : 0;
-  if (ug.group > 1)
-    return each_launch((ug.n_units - 1) / ug.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
-      const dim3 grid(cnt);
-      KVX_LAUNCH_GROUPS(copy_unit_groups_kernel, (kToPacked, kOrdered), ug.n16, ug.group, lp, bt, ug, group,
-                        cnt, order, packed, err);
-    });
+  if constexpr (!kOrdered) {
+    if (ug.group > 1)
+      return each_launch((ug.n_units - 1) / ug.group + 1, 1,
+                         [&](uint32_t group, uint32_t, uint32_t cnt) {
+                           const dim3 grid(cnt);
+                           KVX_LAUNCH_GROUPS(copy_unit_groups_kernel, (kToPacked), ug.n16, ug.group,
+                                             lp, bt, ug, group, cnt, packed, err);
+                         });
+  }
   return each_launch(ug.n_units, ug.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_units_kernel, (kToPacked, kOrdered), lp, bt, ug, unit, part, cnt,
@@ -1493,11 +1485,12 @@ hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk
   const SlabGeom& sg = cg.sg;
   constexpr size_t hold = 0;
   if (cg.group > 1)
-    return each_launch((cg.n_units - 1) / cg.group + 1, 1, [&](uint32_t group, uint32_t, uint32_t cnt) {
-      const dim3 grid(cnt);
-      KVX_LAUNCH_GROUPS(copy_chunk_groups_kernel, (kToPacked), cg.n16, cg.group, lp, bt, refs, cg, group,
-                        cnt, packed, err);
-    });
+    return each_launch((cg.n_units - 1) / cg.group + 1, 1,
+                       [&](uint32_t group, uint32_t, uint32_t cnt) {
+                         const dim3 grid(cnt);
+                         KVX_LAUNCH_GROUPS(copy_chunk_groups_kernel, (kToPacked), cg.n16, cg.group,
+                                           lp, bt, refs, cg, group, cnt, packed, err);
+                       });
   return each_launch(cg.n_units, cg.parts, [&](uint32_t unit, uint32_t part, uint32_t cnt) {
     const dim3 grid(cnt);
     KVX_DISPATCH(copy_chunks_kernel, (kToPacked), lp, bt, refs, cg, unit, part, cnt, packed, err);
