@@ -59,13 +59,13 @@ KERNELS_SRC = [os.path.join(ROOT, "paper_2609_11744_amd", "csrc", f)
 # only for the kernel code they were taken on (kernels_sha256 below); otherwise the
 # bench reports traffic as null.
 GATHER_TRAFFIC = {
-    "kernels_sha256": "96ab12857d16c71ee4cd3fc6458b23157b570131f84e23a98ea96daadf762bfa",
+    "kernels_sha256": "eb180afc0ff9ee82145de8aa76a16af58299d81c25a76a6f0f812f72a8c11cad",
     # cache layout -> (fetched, written) HBM bytes of the timed gather launch
     # at the default 80k-token workload: FETCH_SIZE KiB x 1.999988 (copy
     # calibration), WRITE_SIZE KiB x 1.0
-    "nhd": (10488814621, 10485760000),         # 5,121,521.1 / 10,240,000.0 KiB
-    "paged_attn": (10488986766, 10485760000),  # 5,121,604.9 / 10,240,000.0 KiB
-    "hnd": (10488843210, 10485760000),         # 5,121,536.0 / 10,240,000.0 KiB
+    "nhd": (10488847734, 10485760000),         # 5,121,539.1 / 10,240,000.0 KiB
+    "paged_attn": (10489007206, 10485760000),  # 5,121,616.7 / 10,240,000.0 KiB
+    "hnd": (10488855667, 10485760000),         # 5,121,541.6 / 10,240,000.0 KiB
 }
 
 
