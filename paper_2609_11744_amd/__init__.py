@@ -17,6 +17,7 @@ Operations (sections of the paper they follow):
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 
 from . import _native
@@ -175,7 +176,13 @@ def kvx_packed_bytes(cache, l0, l1, n_blocks) -> int:
 
 def _image_bytes(cache, l0, l1, n_blocks) -> int:
     """kvx_packed_bytes of a call, 0 if the call is invalid (the library says so),
-    without asking the library again for what only the cache's shape decides."""
+    without asking the library again for what only the cache's shape decides.
+    Counted in Python's own integers: a NumPy or tensor scalar, which the library
+    call takes too, would wrap in its 16 or 32 bits."""
+    try:
+        l0, l1, n_blocks = operator.index(l0), operator.index(l1), operator.index(n_blocks)
+    except TypeError:  # the library call converts it, or refuses it
+        return max(kvx_packed_bytes(cache, l0, l1, n_blocks), 0)
     if cache._layer_block is None:
         one = kvx_packed_bytes(cache, 0, 1, 1)
         pieces = kvx_copy_walk(cache, 0, 1, 1, cache.block_size, True)["work_items"] if one > 0 else 0
