@@ -959,7 +959,10 @@ __global__ void __launch_bounds__(kListThreads)
 // second launch from workgroup `first` on, which else end at once: around the
 // LDS phases the loop cost 8 to 25 % (8 x 128 dims, 1 GiB, uneven lists, gather /
 // scatter: bf16 389 / 398 us looped, 357 / 397 in two launches; 8-bit 423 / 510
-// and 372 / 402), around plain moves nothing.
+// and 372 / 402), around plain moves nothing. A list that does share pays for the
+// rounds: 16 requests of four shared 16-block chunks and one of their own, gathered,
+// padded / listed: 32 KiB slabs 877 / 848 us, paged attention 890 / 1098, 8-bit 928 /
+// 1178; 32 such requests of 4 KiB slabs, 80 layers, 572 / 626.
 template <bool kToPacked, bool kLoop, int kLayout, int kElem, bool kOne, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_list_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
@@ -1346,7 +1349,7 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
 
 #define KVX_LAUNCH_TILES(KERNEL, PREFIX, ELEM, ...)                                         \
   do {                                                                                 \
-    const uint32_t n = sg.gh * sg.np.d;                                                \
+    const uint32_t tile = sg.gh * sg.np.d;                                             \
     const bool one = sg.gh == 1 && sg.dpieces.d == 1;                                  \
     constexpr int T = kTransposeThreads;                                               \
     if constexpr (!kToPacked) {                                                        \
@@ -1358,13 +1361,13 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
         break;                                                                         \
       }                                                                                \
     }                                                                                  \
-    if (n <= (uint32_t)T && one)                                                       \
+    if (tile <= (uint32_t)T && one)                                                    \
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, true, T, 1, __VA_ARGS__);                  \
-    else if (n <= (uint32_t)T)                                                         \
+    else if (tile <= (uint32_t)T)                                                      \
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 1, __VA_ARGS__);                 \
-    else if (n <= 2u * T)                                                              \
+    else if (tile <= 2u * T)                                                           \
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 2, __VA_ARGS__);                 \
-    else if (n <= 4u * T)                                                              \
+    else if (tile <= 4u * T)                                                           \
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, 4, __VA_ARGS__);                 \
     else                                                                               \
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, kVecPerThread, __VA_ARGS__);     \

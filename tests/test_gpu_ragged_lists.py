@@ -136,6 +136,33 @@ def test_ragged_lists_sharing_entries_bad_refs_and_ids(case):
     assert first_mismatch(to_host(out), want) is None
 
 
+def test_shared_entries_of_tiles_larger_than_the_second_launch():
+    """2,560-vector tiles of a list with more blocks than its table: the second
+    launch's 2,048 workgroups go round by their own number, not by the tile's
+    vectors (which left 512 of every 2,560 slabs where they were)."""
+    case = (PA, 64, 160, 1, 128, 2, 8, None, 1)
+    _, L, bs, _, _, _, bpc, _, _ = case
+    n, NB = 64, 70
+    s, cache, mirror = _setup(case, NB, 930)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    (ids,) = seeded_ids(930, NB, n)
+    rng = np.random.default_rng(9)
+    refs, off = [], 0
+    for c in range(45):
+        m = 1 + c % 4
+        refs.append((off, int(rng.integers(0, n - m + 1)), m))
+        off += m * per_block
+    assert _listed(case, n, len(refs))
+    # at least one whole round of the second launch, and more
+    assert 2 * L * (sum(r[2] for r in refs) - n) > 2560
+    out = torch.full((off,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids), n, kvx.chunk_refs(refs, DEV), len(refs), bpc * bs,
+                          out)
+    kvx.kvx_check()
+    want = _want(s, mirror, L, ids, refs, off, bs)
+    assert first_mismatch(to_host(out), want) is None
+
+
 def test_ragged_list_under_capture_replays_bit_exact():
     case = CASES[0]
     _, L, bs, _, _, _, bpc, lengths, _ = case
