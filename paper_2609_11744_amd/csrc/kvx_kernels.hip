@@ -1378,10 +1378,10 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
     const uint32_t threads = (sg.piece + 63u) & ~63u;                                  \
     if (layout == KVX_LAYOUT_NHD)                                                      \
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, false, kPartThreads, 1>), \
-                         grid, dim3(threads), hold, stream, __VA_ARGS__);            \
+                         grid, dim3(threads), 0, stream, __VA_ARGS__);               \
     else if (layout == KVX_LAYOUT_HND)                                                 \
       hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, false, kPartThreads, 1>), \
-                         grid, dim3(threads), hold, stream, __VA_ARGS__);            \
+                         grid, dim3(threads), 0, stream, __VA_ARGS__);               \
     else if (elem == 1)                                                                \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 1, __VA_ARGS__);                                 \
     else if (elem == 2)                                                                \
@@ -1391,17 +1391,6 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
     else                                                                               \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 8, __VA_ARGS__);                                 \
   } while (0)
-
-// LDS that a workgroup of a linear-walk scatter reserves, unused, so that six
-// of them run on a compute unit instead of eight: with less of the image in
-// flight the writes land on fewer blocks at a time. 80 layers, 2,048 blocks:
-// 4 KiB slabs 472 -> 463 us, 2 KiB 239 -> 233 us, 8 KiB 710 -> 696 us (1,500
-// blocks); seven per unit 469, 236, 706 us, five 468, 237 us, four 510, 259 us.
-// 32 layers: 4 KiB 361 -> 359 us, 2 KiB level. Slabs below 1 KiB, whose lanes
-// each wait for a block id of their own, lost 1 to 2 %, so they run unheld; so
-// do the ordered walks and the gathers (4 to 5 % slower held to six).
-constexpr size_t kLinearScatterLds = 26624;
-constexpr uint32_t kHeldMinVectors = 64;
 
 // Calls launch(unit_base, part_base, workgroups) for each launch of a copy of
 // n_units slabs of `parts` workgroups each: as many whole slabs as fit
@@ -1441,13 +1430,13 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
     const bool wave = (N16) % 64 == 0;                                                 \
     const size_t lds = 16u * (size_t)sg.image * (GROUP);                               \
     if (layout == KVX_LAYOUT_NHD && wave)                                              \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, true, hold, __VA_ARGS__);     \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, true, 0, __VA_ARGS__);        \
     else if (layout == KVX_LAYOUT_NHD)                                                 \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, false, hold, __VA_ARGS__);    \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, false, 0, __VA_ARGS__);       \
     else if (layout == KVX_LAYOUT_HND && wave)                                         \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, true, hold, __VA_ARGS__);     \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, true, 0, __VA_ARGS__);        \
     else if (layout == KVX_LAYOUT_HND)                                                 \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, false, hold, __VA_ARGS__);    \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, false, 0, __VA_ARGS__);       \
     else if (elem == 1)                                                                \
       KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 1, __VA_ARGS__); \
     else if (elem == 2)                                                                \
@@ -1463,8 +1452,6 @@ hipError_t launch(const LayerPtrs& lp, const int32_t* bt, const UnitGeom& ug,
                   const OrderEntry* order, char* packed, int* err, int layout, int elem,
                   hipStream_t stream) {
   const SlabGeom& sg = ug.sg;
-  const size_t hold =
-      !kToPacked && ug.linear_walk && ug.n16 >= kHeldMinVectors ? kLinearScatterLds : 0;
   if constexpr (!kOrdered) {
     if (ug.group > 1)
       return each_launch((ug.n_units - 1) / ug.group + 1, 1,
@@ -1486,7 +1473,6 @@ hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk
                          const ChunkGeom& cg, char* packed, int* err, int layout, int elem,
                          hipStream_t stream) {
   const SlabGeom& sg = cg.sg;
-  constexpr size_t hold = 0;
   if (cg.group > 1)
     return each_launch((cg.n_units - 1) / cg.group + 1, 1,
                        [&](uint32_t group, uint32_t, uint32_t cnt) {
@@ -1506,7 +1492,6 @@ hipError_t launch_list_copy(const LayerPtrs& lp, const int32_t* bt, const ListBl
                             const uint32_t* count, const ChunkGeom& cg, uint32_t first, uint32_t n,
                             char* packed, int* err, int layout, int elem, hipStream_t stream) {
   const SlabGeom& sg = cg.sg;
-  constexpr size_t hold = 0;
   const dim3 grid(n);
   if (cg.group > 1)
     KVX_LAUNCH_GROUPS(copy_list_groups_kernel, (kToPacked, kLoop), cg.n16, cg.group, lp, bt, blocks,

@@ -90,7 +90,11 @@ namespace {
 // Slabs of several heads in a reordering layout join them where they are grouped
 // (2 KiB, two heads of 64 dims 8-bit, ordered / linear: HND 415 / 387 us, paged
 // attention 400 / 370; 1,920 bytes ordered / image order 430 / 418, 543 / 450;
-// eight-token blocks of two such heads lost 2 to 5 % in the latter).
+// eight-token blocks of two such heads lost 2 to 5 % in the latter). LDS reserved
+// so that six workgroups of a linear walk run on a compute unit, not eight, is not
+// taken: over 12 pairs, held / unheld, 4 KiB slabs 456 / 462 us (80 layers, 2,048
+// blocks), 354 / 354 (32 layers, 4,096) and 94 / 91 (1,100), 8 KiB 637 / 632 and
+// 344 / 340, 2 KiB 215 / 210 and 351 / 343, 1 KiB 176 / 167.
 bool small_rows(int64_t slab, int layout, int32_t heads) {
   return slab <= 16 * (int64_t)kGroupMaxVectors ||
          (slab <= 8192 && (layout == KVX_LAYOUT_NHD || heads == 1));
