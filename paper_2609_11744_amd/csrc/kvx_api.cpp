@@ -123,9 +123,9 @@ static kvx_status chunks_entry(bool to_packed, const kvx_cache* cache, int32_t l
                             : (int64_t)cache->num_kv_heads;
   if (units > INT32_MAX || units * parts > INT32_MAX) return KVX_EINVAL;
   if (overlaps_cache(cache, l0, l1, packed, packed_bytes)) return KVX_EINVAL;
-  return launch_copy_chunks(to_packed, cache, l0, l1, block_table, table_len, chunks, n_chunks,
-                            chunk_tokens, const_cast<void*>(packed), packed_bytes, stream,
-                            stream_error_word(stream));
+  return launch_copy_list(to_packed, cache, l0, l1, block_table, table_len, chunks, n_chunks,
+                          chunk_tokens, const_cast<void*>(packed), packed_bytes, stream,
+                          stream_error_word(stream));
 }
 
 }  // namespace kvx

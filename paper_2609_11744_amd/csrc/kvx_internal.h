@@ -113,14 +113,21 @@ constexpr size_t kNoAllocScratchBytes = (size_t)KVX_NOALLOC_MAX_BLOCKS * 8;
 // Enqueue the chunk-list gather (to_packed) or scatter on `stream`: refs is a
 // device array of n_chunks references, validated by the kernel against
 // table_len and packed_bytes. Host-checkable arguments must already be valid.
-// A list of mostly short chunks, as table_len shows, takes stream-ordered
-// scratch (list_grid, kvx_kernels.hip); with table_len at least n_chunks full
-// chunks a call allocates nothing.
+// Allocates nothing: the ring's copies, whose streams' scratch could come back
+// from another stream's free and wait for it.
 kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
                               const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
                               void* packed, int64_t packed_bytes, hipStream_t stream,
                               int* err);
+
+// The same copy for the list calls: a list of mostly short chunks, as table_len
+// shows, is copied without padding and takes stream-ordered scratch for it
+// (list_grid, kvx_kernels.hip).
+kvx_status launch_copy_list(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
+                            const int32_t* block_table, int32_t table_len,
+                            const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
+                            void* packed, int64_t packed_bytes, hipStream_t stream, int* err);
 
 // A chunk image in host memory (restore source or offload destination) and the
 // block-table slice it belongs to.

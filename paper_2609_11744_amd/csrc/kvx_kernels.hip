@@ -1750,8 +1750,10 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
 
-kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
-                              const int32_t* block_table, int32_t table_len,
+// Both chunk-list launchers; may_list: the copy may run without padding, on
+// stream-ordered scratch (list_grid).
+static kvx_status copy_chunks(bool may_list, bool to_packed, const kvx_cache* cache, int32_t l0,
+                              int32_t l1, const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
                               void* packed, int64_t packed_bytes, hipStream_t stream,
                               int* err) {
@@ -1788,7 +1790,7 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
   cg.sg = slab_geom(cache, to_packed);
   cg.n_chunks = (uint32_t)n_chunks;
   cg.lr2_div = div_u32(cg.lr2);
-  cg.list_grid = list_grid(cg, stream);
+  cg.list_grid = may_list ? list_grid(cg, stream) : 0;
   char* pk = static_cast<char*>(packed);
   hipError_t e;
   uint32_t* scratch = nullptr;
@@ -1812,6 +1814,23 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
                   : launch_chunks<false>(lp, block_table, refs, cg, pk, err, layout, elem, stream);
   }
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
+}
+
+kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
+                              const int32_t* block_table, int32_t table_len,
+                              const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
+                              void* packed, int64_t packed_bytes, hipStream_t stream,
+                              int* err) {
+  return copy_chunks(false, to_packed, cache, l0, l1, block_table, table_len, refs, n_chunks,
+                     chunk_tokens, packed, packed_bytes, stream, err);
+}
+
+kvx_status launch_copy_list(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
+                            const int32_t* block_table, int32_t table_len,
+                            const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
+                            void* packed, int64_t packed_bytes, hipStream_t stream, int* err) {
+  return copy_chunks(true, to_packed, cache, l0, l1, block_table, table_len, refs, n_chunks,
+                     chunk_tokens, packed, packed_bytes, stream, err);
 }
 
 }  // namespace kvx

@@ -687,13 +687,7 @@ void file_drain_worker(kvx_ring* r) {
 
 kvx_status launch_piece(kvx_ring* r, bool to_packed, const kvx::Piece& p, const int32_t* bt,
                         uint8_t* dslot, hipStream_t stream) {
-  // The plan's references keep within plan.table_len by construction. A table of
-  // at least full chunks keeps the copy from taking stream-ordered scratch: a
-  // ring stream's could come back from another stream's free and wait for it.
-  const int64_t full = (int64_t)p.ref_count * (r->chunk_tokens / r->cache.block_size);
-  const int32_t table_len =
-      (int32_t)std::min<int64_t>(std::max<int64_t>(r->plan.table_len, full), INT32_MAX);
-  return kvx::launch_copy_chunks(to_packed, &r->cache, p.l_begin, p.l_end, bt, table_len,
+  return kvx::launch_copy_chunks(to_packed, &r->cache, p.l_begin, p.l_end, bt, r->plan.table_len,
                                  r->d_refs + p.ref_first, p.ref_count, r->chunk_tokens, dslot,
                                  r->slot_bytes, stream, r->err_word);
 }

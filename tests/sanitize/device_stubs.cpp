@@ -17,6 +17,12 @@ kvx_status launch_copy_chunks(bool, const kvx_cache*, int32_t, int32_t, const in
   return KVX_EHIP;
 }
 
+kvx_status launch_copy_list(bool, const kvx_cache*, int32_t, int32_t, const int32_t*, int32_t,
+                            const kvx_chunk_ref*, int32_t, int32_t, void*, int64_t, hipStream_t,
+                            int*) {
+  return KVX_EHIP;
+}
+
 int* stream_error_word(hipStream_t) { return nullptr; }
 
 }  // namespace kvx
