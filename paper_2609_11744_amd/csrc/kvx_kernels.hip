@@ -568,6 +568,11 @@ __device__ __forceinline__ void v_pairs_gather(v4u* __restrict__ dst, const Slab
 // lanes take them: 16-lane group k = w / 16 of (head, 16 tokens, 16 dims); at:
 // its destination offset. 8 x 128 dims, 16 tokens, 1 GiB: gather 365 -> 353 us,
 // scatter 400 -> 385 us against element by element.
+// Every lane of the wave must take part: a transposing read writes the result
+// registers of all 64 lanes, also of those that are switched off, where the
+// compiler may keep another value, such as what the other side of a branch
+// computed. So lanes with nothing to turn give a vector that exists and drop the
+// result.
 typedef int v2i __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ v2i read_tr8(const unsigned char* p) {
@@ -612,7 +617,7 @@ __device__ __forceinline__ void v_bytes_out(v4u* __restrict__ dst, const SlabGeo
   for (int q = 0; q < V; ++q) {
     const uint32_t w = threadIdx.x + q * T;
     ok[q] = w < tile.heads * g.np.d;  // the same for the 16 lanes of a group
-    if (ok[q]) r[q] = v_bytes<kToPacked>(w, g, kvx_lds, g.prow, &at[q]);
+    r[q] = v_bytes<kToPacked>(ok[q] ? w : w & 15u, g, kvx_lds, g.prow, &at[q]);
   }
   const auto out = stream_dst(dst, tile_dst_bytes<kToPacked>(g));
 #pragma unroll
@@ -636,7 +641,7 @@ __device__ __forceinline__ void v_bytes_rows_out(v4u* __restrict__ dst, const Sl
   for (int q = 0; q < V; ++q) {
     const uint32_t w = threadIdx.x + q * T;
     ok[q] = w < tile.heads * g.np.d;
-    if (ok[q]) r[q] = v_bytes<true>(w, g, kvx_lds, g.row.d, &at[q]);
+    r[q] = v_bytes<true>(ok[q] ? w : w & 15u, g, kvx_lds, g.row.d, &at[q]);
   }
   __syncthreads();
 #pragma unroll
@@ -1085,33 +1090,38 @@ __device__ __forceinline__ void move_grouped_paged(const Place& p, uint32_t i, u
       typename std::conditional<kElem == 2, uint16_t,
                                 typename std::conditional<kElem == 4, uint32_t,
                                                           uint64_t>::type>::type>::type E;
-  unsigned char* image = kvx_lds + 16u * (i * g.image);
+  unsigned char* image = kvx_lds + 16u * ((p.ok ? i : 0u) * g.image);
   v4u* lds = reinterpret_cast<v4u*>(image);
   if (p.ok)
     lds[lds_slot<kToPacked, kElem>(w, g)] = __builtin_nontemporal_load(
         reinterpret_cast<const v4u*>(kToPacked ? p.paged : p.packed) + w);
   __syncthreads();
-  v4u v;
-  if (kElem == 1 && kToPacked && g.v_bytes == 2) {  // as v_bytes_rows_out; uniform
-    const bool turn = p.ok && p.kv != 0;
-    uint32_t at;
-    if (turn) v = v_bytes<true>(w, g, image, g.row.d, &at);
+  v4u v = {};
+  uint32_t to = w;
+  const bool turn = p.ok && p.kv != 0;
+  if (kElem == 1 && g.v_bytes) {
+    // a wave can hold K and V: all of its lanes take part in the transposing reads
+    v4u turned = {};
+    uint32_t at = 0;
+    const bool rows = kToPacked && g.v_bytes == 2;  // as v_bytes_rows_out
+    if (__builtin_amdgcn_ballot_w64(turn))
+      turned = v_bytes<kToPacked>(w, g, image, rows ? g.row.d : g.prow, &at);
+    if (turn) v = turned;
     else if (p.ok) v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
-    __syncthreads();
-    if (turn) lds[at] = v;
-    __syncthreads();
-    if (turn) v = lds[w];
-    if (p.ok) store_grouped<kWave>(p.base, p.packed, g.n16.d, w, v);
-    return;
-  }
-  if (!p.ok) return;
-  if (p.kv == 0)
-    v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
-  else if (kElem == 1 && g.v_bytes)
-    v = v_bytes<kToPacked>(w, g, image, g.prow, &w);
-  else
+    if (rows) {
+      __syncthreads();
+      if (turn) lds[at] = v;
+      __syncthreads();
+      if (turn) v = lds[w];
+    } else if (turn) {
+      to = at;
+    }
+  } else if (turn) {
     v = v_elements<kToPacked, false, E>(w, g, image);
-  store_grouped<kWave>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, w, v);
+  } else if (p.ok) {
+    v = lds[lds_slot<kToPacked, kElem>(k_source<kToPacked, false>(w, g), g)];
+  }
+  if (p.ok) store_grouped<kWave>(p.base, kToPacked ? p.packed : p.paged, g.n16.d, to, v);
 }
 
 // Unit u of a grouped call, in image order (slabs this small take no other:

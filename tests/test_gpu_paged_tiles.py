@@ -114,3 +114,50 @@ def test_paged_tile_chunk_lists_bit_exact(shape):
     for (_, a, m), img in zip(refs, images):
         oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, img)
     _same_cache(cache, mirror, L)
+
+
+MIXED = [
+    # 8-bit (block, heads, dim): vectors per slab, several slabs per workgroup
+    (16, 1, 16),   # 16: a half-wave holds two slabs
+    (16, 1, 48),   # 48: a slab ends inside a half-wave
+    (16, 1, 80),   # 80
+    (16, 1, 112),  # 112
+    (16, 3, 16),   # 48, three heads
+    (32, 1, 48),   # 96
+    (16, 1, 64),   # 64: a slab a wave
+    (16, 1, 32),   # 32: a slab a half-wave
+]
+
+
+@pytest.mark.parametrize("shape", MIXED, ids=[f"x{i}" for i in range(len(MIXED))])
+def test_keys_and_values_in_one_wave(shape):
+    """Slabs of 8-bit words so small that a wave, and half of one, holds keys of one
+    slab and values of the next: only the values are turned. In one-block chunks
+    every second slab is a value slab; in others the last key slab of a layer meets
+    the first value slab."""
+    bs, h, d = shape
+    L, n = 3, 23
+    NB = 2 * n + 3
+    s, cache, mirror = _setup((bs, h, d, 1), L, NB, 850)
+    src, dst_ids = seeded_ids(850, NB, n, n)
+    for bpc in (1, 4):
+        expect = oracle.gather(s, *mirror, 0, L, src, bpc * bs)
+        out = torch.full((expect.size,), 0xA5, dtype=torch.uint8, device=DEV)
+        kvx.kvx_gather_blocks(cache, 0, L, _bt(src), n, bpc * bs, out)
+        kvx.kvx_check()
+        assert first_mismatch(to_host(out), expect) is None, bpc
+        kvx.kvx_scatter_blocks(cache, 0, L, _bt(dst_ids), n, bpc * bs, out)
+        kvx.kvx_check()
+        oracle.scatter(s, *mirror, 0, L, dst_ids, bpc * bs, expect)
+        _same_cache(cache, mirror, L)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    refs = [(i * per_block, i, 1) for i in range(n)]  # chunks of two blocks, half full
+    out = torch.full((n * per_block,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(src), n, kvx.chunk_refs(refs, DEV), n, 2 * bs, out)
+    kvx.kvx_check()
+    want = oracle.gather(s, *mirror, 0, L, src, bs)
+    assert first_mismatch(to_host(out), want) is None
+    kvx.kvx_scatter_chunks(cache, 0, L, _bt(dst_ids), n, kvx.chunk_refs(refs, DEV), n, 2 * bs, out)
+    kvx.kvx_check()
+    oracle.scatter(s, *mirror, 0, L, dst_ids, bs, want)
+    _same_cache(cache, mirror, L)
