@@ -103,9 +103,7 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f) {
 // Shape of one head's part of a slab, for the reordering layouts.
 struct SlabGeom {
   FastDiv bs;      // tokens per block
-  FastDiv d;       // head dim (elements)
-  FastDiv v16;     // 16-byte vectors per (token, head) row: d * elem_bytes / 16
-  uint32_t x;      // elements per 16-byte vector: 16 / elem_bytes
+  FastDiv v16;     // 16-byte vectors per (token, head) row: head_dim * elem_bytes / 16
   uint32_t nh;     // vectors of one head: bs * v16
   uint32_t prow;   // packed row stride in vectors: heads * v16
   // Paged attention: a workgroup moves a tile of `gh` whole heads, or of `dw` of
@@ -1383,16 +1381,9 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
       KVX_LAUNCH_TILE(KERNEL, PREFIX, ELEM, false, T, kVecPerThread, __VA_ARGS__);     \
   } while (0)
 
-#define KVX_DISPATCH(KERNEL, PREFIX, ...)                                                   \
+#define KVX_DISPATCH_PAGED(KERNEL, PREFIX, ...)                                             \
   do {                                                                                 \
-    const uint32_t threads = (sg.piece + 63u) & ~63u;                                  \
-    if (layout == KVX_LAYOUT_NHD)                                                      \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, false, kPartThreads, 1>), \
-                         grid, dim3(threads), 0, stream, __VA_ARGS__);               \
-    else if (layout == KVX_LAYOUT_HND)                                                 \
-      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, false, kPartThreads, 1>), \
-                         grid, dim3(threads), 0, stream, __VA_ARGS__);               \
-    else if (elem == 1)                                                                \
+    if (elem == 1)                                                                     \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 1, __VA_ARGS__);                                 \
     else if (elem == 2)                                                                \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 2, __VA_ARGS__);                                 \
@@ -1400,6 +1391,19 @@ inline size_t tile_lds(const SlabGeom& sg, uint32_t T, uint32_t V) {
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 4, __VA_ARGS__);                                 \
     else                                                                               \
       KVX_LAUNCH_TILES(KERNEL, PREFIX, 8, __VA_ARGS__);                                 \
+  } while (0)
+
+#define KVX_DISPATCH(KERNEL, PREFIX, ...)                                                   \
+  do {                                                                                 \
+    const uint32_t threads = (sg.piece + 63u) & ~63u;                                  \
+    if (layout == KVX_LAYOUT_NHD)                                                      \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_NHD, 0, false, kPartThreads, 1>), \
+                         grid, dim3(threads), 0, stream, __VA_ARGS__);                 \
+    else if (layout == KVX_LAYOUT_HND)                                                 \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, KVX_LAYOUT_HND, 0, false, kPartThreads, 1>), \
+                         grid, dim3(threads), 0, stream, __VA_ARGS__);                 \
+    else                                                                               \
+      KVX_DISPATCH_PAGED(KERNEL, PREFIX, __VA_ARGS__);                                 \
   } while (0)
 
 // Calls launch(unit_base, part_base, workgroups) for each launch of a copy of
@@ -1423,38 +1427,37 @@ hipError_t each_launch(uint32_t n_units, uint32_t parts, F launch) {
 
 // Launch the grouped kernel of a copy of slabs of N16 vectors, GROUP of them per
 // workgroup (paged attention: an LDS image each).
-#define KVX_LAUNCH_GROUP(KERNEL, PREFIX, LAYOUT, ELEM, WAVE, LDS, ...)                      \
-  hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, WAVE>), grid,           \
-                     dim3(kPartThreads), LDS, stream, __VA_ARGS__)
-
-#define KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, ELEM, ...)                                   \
+#define KVX_LAUNCH_GROUP(KERNEL, PREFIX, LAYOUT, ELEM, LDS, N16, ...)                       \
   do {                                                                                 \
-    if (wave)                                                                          \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, true, lds, __VA_ARGS__); \
+    if ((N16) % 64 == 0)                                                               \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, true>), grid,       \
+                         dim3(kPartThreads), LDS, stream, __VA_ARGS__);                \
     else                                                                               \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, ELEM, false, lds, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<KVX_UNPAREN PREFIX, LAYOUT, ELEM, false>), grid,      \
+                         dim3(kPartThreads), LDS, stream, __VA_ARGS__);                \
+  } while (0)
+
+#define KVX_LAUNCH_GROUPS_PAGED(KERNEL, PREFIX, N16, GROUP, ...)                            \
+  do {                                                                                 \
+    const size_t lds = 16u * (size_t)sg.image * (GROUP);                               \
+    if (elem == 1)                                                                     \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 1, lds, N16, __VA_ARGS__); \
+    else if (elem == 2)                                                                \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 2, lds, N16, __VA_ARGS__); \
+    else if (elem == 4)                                                                \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 4, lds, N16, __VA_ARGS__); \
+    else                                                                               \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_PAGED_ATTN, 8, lds, N16, __VA_ARGS__); \
   } while (0)
 
 #define KVX_LAUNCH_GROUPS(KERNEL, PREFIX, N16, GROUP, ...)                                  \
   do {                                                                                 \
-    const bool wave = (N16) % 64 == 0;                                                 \
-    const size_t lds = 16u * (size_t)sg.image * (GROUP);                               \
-    if (layout == KVX_LAYOUT_NHD && wave)                                              \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, true, 0, __VA_ARGS__);        \
-    else if (layout == KVX_LAYOUT_NHD)                                                 \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, false, 0, __VA_ARGS__);       \
-    else if (layout == KVX_LAYOUT_HND && wave)                                         \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, true, 0, __VA_ARGS__);        \
+    if (layout == KVX_LAYOUT_NHD)                                                      \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_NHD, 0, 0, N16, __VA_ARGS__);         \
     else if (layout == KVX_LAYOUT_HND)                                                 \
-      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, false, 0, __VA_ARGS__);       \
-    else if (elem == 1)                                                                \
-      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 1, __VA_ARGS__); \
-    else if (elem == 2)                                                                \
-      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 2, __VA_ARGS__); \
-    else if (elem == 4)                                                                \
-      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 4, __VA_ARGS__); \
+      KVX_LAUNCH_GROUP(KERNEL, PREFIX, KVX_LAYOUT_HND, 0, 0, N16, __VA_ARGS__);         \
     else                                                                               \
-      KVX_LAUNCH_GROUP_PAGED(KERNEL, PREFIX, 8, __VA_ARGS__); \
+      KVX_LAUNCH_GROUPS_PAGED(KERNEL, PREFIX, N16, GROUP, __VA_ARGS__);                \
   } while (0)
 
 template <bool kToPacked, bool kOrdered>
@@ -1496,19 +1499,29 @@ hipError_t launch_chunks(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk
   });
 }
 
-// Workgroups `first` and up of a list copy, `n` of them.
+// Workgroups `first` and up of a list copy, `n` of them; kLoop: the second launch
+// of paged attention.
 template <bool kToPacked, bool kLoop>
 hipError_t launch_list_copy(const LayerPtrs& lp, const int32_t* bt, const ListBlock* blocks,
                             const uint32_t* count, const ChunkGeom& cg, uint32_t first, uint32_t n,
                             char* packed, int* err, int layout, int elem, hipStream_t stream) {
   const SlabGeom& sg = cg.sg;
   const dim3 grid(n);
-  if (cg.group > 1)
-    KVX_LAUNCH_GROUPS(copy_list_groups_kernel, (kToPacked, kLoop), cg.n16, cg.group, lp, bt, blocks,
-                      count, cg, first, n, packed, err);
-  else
-    KVX_DISPATCH(copy_list_kernel, (kToPacked, kLoop), lp, bt, blocks, count, cg, first, n, packed,
-                 err);
+  if constexpr (kLoop) {
+    if (cg.group > 1)
+      KVX_LAUNCH_GROUPS_PAGED(copy_list_groups_kernel, (kToPacked, true), cg.n16, cg.group, lp, bt,
+                              blocks, count, cg, first, n, packed, err);
+    else
+      KVX_DISPATCH_PAGED(copy_list_kernel, (kToPacked, true), lp, bt, blocks, count, cg, first, n,
+                         packed, err);
+  } else {
+    if (cg.group > 1)
+      KVX_LAUNCH_GROUPS(copy_list_groups_kernel, (kToPacked, false), cg.n16, cg.group, lp, bt,
+                        blocks, count, cg, first, n, packed, err);
+    else
+      KVX_DISPATCH(copy_list_kernel, (kToPacked, false), lp, bt, blocks, count, cg, first, n,
+                   packed, err);
+  }
   return hipGetLastError();
 }
 
@@ -1603,13 +1616,11 @@ uint32_t piece_vectors(uint32_t n16) {
 // no LDS.
 SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
   const uint32_t bs = (uint32_t)c->block_size, h = (uint32_t)c->num_kv_heads,
-                 d = (uint32_t)c->head_dim, x = (uint32_t)(16 / c->elem_bytes),
-                 v16 = (uint32_t)((int64_t)c->head_dim * c->elem_bytes / 16);
+                 v16 = (uint32_t)((int64_t)c->head_dim * c->elem_bytes / 16),
+                 n16 = (uint32_t)((int64_t)bs * h * c->head_dim * c->elem_bytes / 16);
   SlabGeom sg = {};
   sg.bs = fast_div(bs);
-  sg.d = fast_div(d);
   sg.v16 = fast_div(v16 ? v16 : 1);
-  sg.x = x;
   sg.nh = bs * v16;
   sg.prow = h * v16;
   sg.heads = h;
@@ -1622,8 +1633,8 @@ SlabGeom slab_geom(const kvx_cache* c, bool to_packed) {
     sg.np = fast_div(bs * tile.vectors);
     sg.dwd = fast_div(tile.vectors);
   }
-  sg.piece = piece_vectors((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
-  sg.n16 = fast_div((uint32_t)((int64_t)bs * h * d * c->elem_bytes / 16));
+  sg.piece = piece_vectors(n16);
+  sg.n16 = fast_div(n16);
   sg.outer = fast_div(to_packed ? sg.prow : sg.nh);
   sg.src_step = to_packed ? sg.nh : sg.prow;
   // V of 2-byte words as row pairs in a gather: token pairs, so an even

@@ -195,10 +195,10 @@ kvx_status choose_walk(bool to_packed, const kvx_cache* cache, const Geometry& g
   if ((uint64_t)g.n_units * w->pieces > 0x7FFFFFFF) return KVX_EINTERNAL;
   copy_parts(cache, n16, &w->parts, &w->parts_shift);
   const uint64_t n_work = (uint64_t)g.n_units * w->parts;
-  // Pairs are chosen where both the pieces and the workgroups of a slab are a
-  // power of two and slabs are not grouped.
-  const uint32_t pair_parts =
-      w->pieces & (w->pieces - 1) || copy_group(n16) > 1 ? 32u : w->parts_shift;
+  // No pairs where slabs are grouped: they need none (gathers of 2 KiB slabs in
+  // 64-block chunks, D = 16, 32 and 80 layers: 407 and 506 us paired with a slab per
+  // workgroup, 356 and 440 grouped and unpaired).
+  const uint32_t pair_parts = copy_group(n16) > 1 ? 32u : w->parts_shift;
   const uint32_t n_slices = (uint32_t)(2 * g.lr);
   if (to_packed) {
     w->gather_pair_shift = gather_pairing(pair_parts, n_slices, (uint32_t)g.bpc,
