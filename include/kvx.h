@@ -224,8 +224,12 @@ typedef struct kvx_chunk_ref {
  *   block_table  device int32[table_len]
  *   packed       device, 16-byte aligned, packed_bytes bytes; must not
  *                overlap any cache tensor
- * A list of mostly short chunks, by n_chunks, chunk_tokens and table_len, takes
- * stream-ordered scratch for the call, except on a capturing stream.
+ * A list of mostly short chunks, by n_chunks, chunk_tokens and table_len, is
+ * listed block by block in device memory of the library's (8 MiB a GPU until the
+ * process ends, in four parts), except on a capturing stream. Nothing is
+ * allocated and the host does not wait. A stream keeps its part; one without a part
+ * takes the least recently used one and, on the device, waits for the list call
+ * that had it, so list calls on up to four streams do not wait for each other.
  * Host-checkable errors as for kvx_gather_blocks (KVX_EINVAL), plus a launch
  * too large for 32-bit unit indexes (n_chunks * (l1 - l0) * 2 * blocks per
  * chunk >= 2^31). The refs live on the device and are checked by the kernel:

@@ -113,8 +113,7 @@ constexpr size_t kNoAllocScratchBytes = (size_t)KVX_NOALLOC_MAX_BLOCKS * 8;
 // Enqueue the chunk-list gather (to_packed) or scatter on `stream`: refs is a
 // device array of n_chunks references, validated by the kernel against
 // table_len and packed_bytes. Host-checkable arguments must already be valid.
-// Allocates nothing: the ring's copies, whose streams' scratch could come back
-// from another stream's free and wait for it.
+// Takes no scratch, so that the ring's streams share none with the caller's.
 kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
                               const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
@@ -122,8 +121,8 @@ kvx_status launch_copy_chunks(bool to_packed, const kvx_cache* cache, int32_t l0
                               int* err);
 
 // The same copy for the list calls: a list of mostly short chunks, as table_len
-// shows, is copied without padding and takes stream-ordered scratch for it
-// (list_grid, kvx_kernels.hip).
+// shows, is copied without padding, through a slot of the device's list scratch
+// (list_grid, take_list_slot, kvx_kernels.hip).
 kvx_status launch_copy_list(bool to_packed, const kvx_cache* cache, int32_t l0, int32_t l1,
                             const int32_t* block_table, int32_t table_len,
                             const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,

@@ -892,7 +892,7 @@ static_assert(sizeof(ListBlock) == 32, "one scalar load");
 constexpr uint32_t kListThreads = 256;
 constexpr uint32_t kListChunks = 64;    // chunks per workgroup of list_kernel
 constexpr uint32_t kListMaxChunks = 4096;  // each workgroup sums the blocks of all chunks before its own
-constexpr uint64_t kListMaxBlocks = 1u << 21;  // 64 MiB of entries
+constexpr uint64_t kListMaxBlocks = 1u << 16;  // 2 MiB of entries
 
 // Blocks of chunk c, or 0 for a bad reference.
 __device__ __forceinline__ uint32_t list_blocks(const kvx_chunk_ref* refs, uint32_t c,
@@ -1525,12 +1525,13 @@ hipError_t launch_list_copy(const LayerPtrs& lp, const int32_t* bt, const ListBl
   return hipGetLastError();
 }
 
-// The list's blocks counted and listed in scratch, then one copy over them.
+// The list's blocks counted and listed in `scratch` (a slot's: take_list_slot),
+// then one copy over them.
 template <bool kToPacked>
 hipError_t launch_list(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_ref* refs,
                        const ChunkGeom& cg, uint32_t* scratch, char* packed, int* err, int layout,
                        int elem, hipStream_t stream) {
-  ListBlock* blocks = reinterpret_cast<ListBlock*>(scratch + 8);
+  ListBlock* blocks = reinterpret_cast<ListBlock*>(scratch + 64);
   const bool pair = kToPacked && cg.parts_shift < 32 && cg.group == 1;
   hipLaunchKernelGGL(list_kernel, dim3((cg.n_chunks + kListChunks - 1) / kListChunks),
                      dim3(kListThreads), 0, stream, refs, cg, pair ? 1u : 0u, blocks, scratch,
@@ -1548,13 +1549,15 @@ hipError_t launch_list(const LayerPtrs& lp, const int32_t* bt, const kvx_chunk_r
 
 // Workgroups of a list copy without padding, or 0 where the padded copy is
 // taken: few padding workgroups by the table's length (a list's chunks hardly
-// ever share table entries) against the 12 us that the listing and its scratch
-// cost, as long as the card takes to dispatch 20,000 workgroups (65 us padded, 57
-// listed, with 38,000 of them); more units than a
-// launch takes; or a capturing stream, on which nothing is allocated. Nor lists
-// of less than 32 MiB or so, which run in less than the 24 us of host time that
-// the scratch takes (17 MiB in 6 chunks of 1 or 2 of 16 blocks: 22 us
-// padded, 26 listed).
+// ever share table entries); little to move; more blocks than a slot has entries;
+// more units than a launch takes; or a capturing stream, whose graph would use a
+// slot without waiting for it. The lines at 32,768 padding workgroups and 8,192
+// others were drawn when a call's scratch took 12 us of its stream and 24 us of the
+// host (65 us padded, 57 listed, with 38,000 padding workgroups). With slots a
+// listed call takes 10 us of the host, a padded one 5, and the listed copy is level
+// below 16 MiB and ahead from there: chunks of 1 to 16 of 16 blocks, 32 layers of
+// 32 KiB slabs, padded / listed, 8 MiB 10.8 / 10.9 us, 24 MiB 17.7 / 17.1, 48 MiB
+// 28.7 / 23.9, 128 MiB 57.9 / 54.3, 256 MiB 119.0 / 95.3.
 uint32_t list_grid(const ChunkGeom& g, hipStream_t stream) {
   const uint64_t padded = (uint64_t)g.n_chunks * g.bpc, table = (uint64_t)g.table_len;
   if (table >= padded || g.n_chunks > kListMaxChunks || padded > kListMaxBlocks) return 0;
@@ -1667,6 +1670,64 @@ struct ErrorTable {
 ErrorTable g_tables[kMaxDevices];
 std::mutex g_tables_mu;
 
+// ---- scratch of the list copies without padding --------------------------------
+//
+// A fixed array, cut into slots (count, then one entry per block): stream-ordered
+// allocations made a call wait, on the host, for the list call before it. A stream
+// keeps the slot it used last and is in order with itself; a stream without one
+// takes the slot that was used longest ago and waits on the device for the copy
+// that had it. Calls are so independent on up to kListSlots streams. The event of
+// a slot is recorded behind each copy; waiting for it also covers a stream that
+// was destroyed and whose handle another one got.
+constexpr int kListSlots = 4;
+constexpr size_t kListSlotBytes = 256 + kListMaxBlocks * sizeof(ListBlock);
+static __device__ __align__(256) unsigned char g_list_scratch[kListSlots * kListSlotBytes];
+
+struct ListSlot {
+  hipStream_t stream = nullptr;
+  hipEvent_t done = nullptr;
+  uint64_t used = 0;  // when, in the device's list copies; 0: never
+};
+
+struct ListSlots {
+  char* base = nullptr;
+  uint64_t copies = 0;
+  ListSlot slot[kListSlots];
+};
+
+ListSlots g_list_slots[kMaxDevices];
+std::mutex g_list_mu;  // held from taking a slot until its event is recorded
+
+// The calling device's slot for a list copy on `stream`, which is made to wait
+// for the slot's last copy, and the slot's memory; null if that fails.
+ListSlot* take_list_slot(hipStream_t stream, uint32_t** scratch) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+  ListSlots& t = g_list_slots[dev];
+  if (!t.base) {
+    void* p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_list_scratch)) != hipSuccess) return nullptr;
+    t.base = (char*)p;
+  }
+  ListSlot* s = t.slot;
+  for (ListSlot& c : t.slot) {
+    if (c.used && c.stream == stream) {
+      s = &c;
+      break;
+    }
+    if (c.used < s->used) s = &c;
+  }
+  if (!s->done && hipEventCreateWithFlags(&s->done, hipEventDisableTiming) != hipSuccess) {
+    s->done = nullptr;
+    return nullptr;
+  }
+  if (s->used && hipStreamWaitEvent(stream, s->done, 0) != hipSuccess) return nullptr;
+  s->stream = stream;
+  s->used = ++t.copies;
+  *scratch = reinterpret_cast<uint32_t*>(t.base + (size_t)(s - t.slot) * kListSlotBytes);
+  return s;
+}
+
 }  // namespace
 
 int* stream_error_word(hipStream_t stream) {
@@ -1771,8 +1832,7 @@ kvx_status launch_copy(bool to_packed, const kvx_cache* cache, int32_t l0, int32
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
 
-// Both chunk-list launchers; may_list: the copy may run without padding, on
-// stream-ordered scratch (list_grid).
+// Both chunk-list launchers; may_list: the copy may run without padding (list_grid).
 static kvx_status copy_chunks(bool may_list, bool to_packed, const kvx_cache* cache, int32_t l0,
                               int32_t l1, const int32_t* block_table, int32_t table_len,
                               const kvx_chunk_ref* refs, int32_t n_chunks, int32_t chunk_tokens,
@@ -1814,26 +1874,22 @@ static kvx_status copy_chunks(bool may_list, bool to_packed, const kvx_cache* ca
   cg.list_grid = may_list ? list_grid(cg, stream) : 0;
   char* pk = static_cast<char*>(packed);
   hipError_t e;
-  uint32_t* scratch = nullptr;
   if (cg.list_grid) {
-    // one entry per block the list can have, after the count
-    const size_t bytes = 32 + (size_t)n_chunks * bpc * sizeof(ListBlock);
-    if (hipMallocAsync((void**)&scratch, bytes, stream) != hipSuccess) {
-      (void)hipGetLastError();
-      scratch = nullptr;  // the padded copy needs none
+    std::lock_guard<std::mutex> lock(g_list_mu);
+    uint32_t* scratch = nullptr;
+    if (ListSlot* slot = take_list_slot(stream, &scratch)) {
+      e = to_packed ? launch_list<true>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
+                                        stream)
+                    : launch_list<false>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
+                                         stream);
+      hipError_t er = hipEventRecord(slot->done, stream);
+      if (er != hipSuccess) (void)hipStreamSynchronize(stream);  // nothing left to wait for
+      return e == hipSuccess && er == hipSuccess ? KVX_OK : KVX_EHIP;
     }
+    (void)hipGetLastError();  // the padded copy needs no slot
   }
-  if (scratch) {
-    e = to_packed ? launch_list<true>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
-                                      stream)
-                  : launch_list<false>(lp, block_table, refs, cg, scratch, pk, err, layout, elem,
-                                       stream);
-    const hipError_t ef = hipFreeAsync(scratch, stream);
-    if (e == hipSuccess) e = ef;
-  } else {
-    e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, pk, err, layout, elem, stream)
-                  : launch_chunks<false>(lp, block_table, refs, cg, pk, err, layout, elem, stream);
-  }
+  e = to_packed ? launch_chunks<true>(lp, block_table, refs, cg, pk, err, layout, elem, stream)
+                : launch_chunks<false>(lp, block_table, refs, cg, pk, err, layout, elem, stream);
   return e == hipSuccess ? KVX_OK : KVX_EHIP;
 }
 

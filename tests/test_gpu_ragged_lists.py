@@ -2,8 +2,12 @@
 layout and grouping, more chunks than one listing workgroup takes, chunks whose
 slices lie 2 MiB apart (the paired gather), chunks that share table entries (more
 blocks than the table has: workgroups go round again), bad references and bad
-block ids, and the same list while a stream is capturing (the padded copy).
+block ids, the same list while a stream is capturing (the padded copy), list calls
+that return before their stream has done anything, on more streams than there are
+slots for their scratch, from several threads, and beside another stream's capture.
 Everything is compared whole with the oracle."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -185,4 +189,96 @@ def test_ragged_list_under_capture_replays_bit_exact():
         torch.cuda.synchronize()
         g.replay()
         kvx.kvx_check()
+        assert first_mismatch(to_host(out), want) is None, f"replay {rep}"
+
+
+def _streams_setup(n_streams, seed):
+    """One cache, and per stream a list of its own, its output and what it must hold."""
+    case = CASES[0]
+    _, L, bs, _, _, _, bpc, lengths, _ = case
+    NB = 2 * sum(lengths) + 3
+    s, cache, mirror = _setup(case, NB, seed)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    jobs = []
+    for k in range(n_streams):
+        some = lengths[k:] + lengths[:k]
+        assert _listed(case, sum(some), len(some))
+        refs, table_len, size = _refs(some, per_block, gap=16 * k)
+        (ids,) = seeded_ids(seed + k, NB, table_len)
+        args = (cache, 0, L, _bt(ids), table_len, kvx.chunk_refs(refs, DEV), len(refs), bpc * bs)
+        out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+        jobs.append((args, out, _want(s, mirror, L, ids, refs, size, bs)))
+    torch.cuda.synchronize()
+    return jobs
+
+
+def test_ragged_lists_do_not_wait_on_the_host():
+    """List calls behind a busy stream return while it is still busy, each of them
+    (stream-ordered scratch made the second wait for the first)."""
+    ((args, out, want),) = _streams_setup(1, 940)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        kvx.kvx_gather_chunks(*args, out)  # whatever a first call sets up
+    torch.cuda.synchronize()
+    out.fill_(0xA5)
+    torch.cuda.synchronize()
+    slept = torch.cuda.Event()
+    with torch.cuda.stream(st):
+        torch.cuda._sleep(500_000_000)  # some 0.2 s
+        slept.record()
+        for _ in range(4):
+            kvx.kvx_gather_chunks(*args, out)
+    assert not slept.query()
+    torch.cuda.synchronize()
+    kvx.kvx_check(st)
+    assert first_mismatch(to_host(out), want) is None
+
+
+def test_ragged_lists_on_many_streams_and_threads():
+    """Seven streams, more than have scratch of their own, called in turn and then
+    each by a thread of its own."""
+    jobs = _streams_setup(7, 950)
+    streams = [torch.cuda.Stream() for _ in jobs]
+
+    def run(k, times):
+        args, out, _ = jobs[k]
+        for _ in range(times):
+            kvx.kvx_gather_chunks(*args, out, stream=streams[k])
+
+    def same():
+        torch.cuda.synchronize()
+        for k, (_, out, want) in enumerate(jobs):
+            kvx.kvx_check(streams[k])
+            assert first_mismatch(to_host(out), want) is None, f"stream {k}"
+            out.fill_(0xA5)
+        torch.cuda.synchronize()
+
+    for _ in range(5):
+        for k in range(len(jobs)):
+            run(k, 1)
+    same()
+    threads = [threading.Thread(target=run, args=(k, 10)) for k in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    same()
+
+
+def test_ragged_list_beside_another_streams_capture():
+    (args, out, want), (args2, out2, want2) = _streams_setup(2, 960)
+    side, own = torch.cuda.Stream(), torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        kvx.kvx_gather_chunks(*args, out)
+        kvx.kvx_gather_chunks(*args2, out2, stream=own)  # runs at once
+    torch.cuda.synchronize()
+    kvx.kvx_check(own)
+    assert first_mismatch(to_host(out2), want2) is None
+    for rep in range(3):
+        out.fill_(0xA5)
+        torch.cuda.synchronize()
+        g.replay()
+        kvx.kvx_check()
+        kvx.kvx_gather_chunks(*args2, out2)
         assert first_mismatch(to_host(out), want) is None, f"replay {rep}"
