@@ -78,6 +78,29 @@ def host_mirror(shape: Shape, fill: Filled, block_ids, layers=None, threads=16):
     return k, v
 
 
+def device_table(ids, device):
+    """A block table on the device."""
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(device)
+
+
+def cache_and_mirror(shape: Shape, seed: int, device):
+    """A device cache of raw generator words, and the whole of it as a host mirror."""
+    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
+    return device_cache(shape, fill, device), host_mirror(shape, fill, range(shape.num_blocks))
+
+
+def check_cache_equals(cache, mirror, num_layers: int) -> None:
+    """Every byte of the device cache against a host mirror."""
+    import torch
+
+    torch.cuda.synchronize()
+    for l in range(num_layers):
+        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
+        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
+
+
 def read_slabs(cache, layer: int, kv: int, ids) -> np.ndarray:
     """Bytes of the given blocks of one cache tensor, as [len(ids), slab] uint8."""
     import torch

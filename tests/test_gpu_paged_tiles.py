@@ -1,15 +1,15 @@
 """Paged-attention tiles: several small heads per workgroup (with and without
-heads left over), one head, a head cut along its rows with one, two and four
-vectors a thread, a head that no piece of whole lines divides, and 8-bit
+heads left over), one head, a head cut along its rows, tiles of one, two, four and
+twelve vectors a thread, a head that no piece of whole lines divides, and 8-bit
 transposes with blocks that are and are not a multiple of 16 tokens; gather and
 scatter in image and in destination order, and chunk lists. Everything is
 compared whole with the oracle."""
 import numpy as np
 import pytest
 
-import kvsynth
 import oracle
-from kvtest_util import Filled, device_cache, first_mismatch, host_mirror, seeded_ids, to_host
+from kvtest_util import (cache_and_mirror, check_cache_equals, device_table, first_mismatch,
+                         seeded_ids, to_host)
 
 torch = pytest.importorskip("torch")
 import paper_2609_11744_amd as kvx  # noqa: E402
@@ -22,7 +22,7 @@ SHAPES = [
     # (block, heads, dim, elem): tile
     (16, 8, 128, 1),    # two heads of 128 vectors
     (16, 5, 128, 1),    # the same, one head left over
-    (16, 3, 96, 1),     # two heads of 96, one left over
+    (16, 3, 96, 1),     # three heads of 96 (all the slab), two a thread
     (16, 4, 64, 1),     # four heads of 64
     (16, 7, 64, 2),     # two heads of 128, one left over
     (8, 3, 80, 2),      # three heads of 80
@@ -32,43 +32,33 @@ SHAPES = [
     (1, 3, 48, 2),      # one token a block
     (16, 2, 256, 2),    # 512 vectors a head: rows cut in halves
     (32, 4, 128, 2),    # the same with 32 tokens
-    (32, 2, 96, 2),     # 384 vectors: no even line piece, two a thread
-    (64, 2, 128, 2),    # 1,024 vectors: halves, two a thread
-    (128, 1, 128, 2),   # 2,048 vectors: halves, four a thread
-    (160, 1, 128, 2),   # 2,560: twelve a thread
+    (32, 2, 96, 2),     # two heads of 384: no even line piece, four a thread
+    (64, 2, 128, 2),    # a head of 1,024, four a thread
+    (128, 1, 128, 2),   # 2,048, twelve a thread
+    (160, 1, 128, 2),   # 2,560, the same
     (64, 3, 128, 1),    # 512 vectors, two a thread
     (32, 3, 128, 1),    # 256 vectors
-    (48, 2, 80, 1),     # 240 vectors
+    (48, 2, 80, 1),     # two heads of 240, two a thread
     (24, 2, 128, 1),    # 8-bit, 24 tokens a block
     (20, 2, 64, 1),     # 8-bit, 20 tokens
-    (16, 3, 80, 4),     # 4-byte words: 320 vectors a head
+    (16, 3, 80, 4),     # 4-byte words: three heads of 320, four a thread
     (8, 2, 256, 4),     # 512 vectors, halves
     (4, 3, 32, 8),      # 8-byte words
 ]
 
 
 def _bt(ids):
-    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(DEV)
+    return device_table(ids, DEV)
 
 
 def _setup(shape, L, NB, seed):
     bs, h, d, e = shape
     s = oracle.Shape(L, NB, bs, h, d, e, PA)
-    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
-    return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
+    return (s, *cache_and_mirror(s, seed, DEV))
 
 
-def _same_cache(cache, mirror, L):
-    torch.cuda.synchronize()
-    for l in range(L):
-        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
-        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
-
-
-@pytest.mark.parametrize("shape", SHAPES, ids=[f"p{i}" for i in range(len(SHAPES))])
-@pytest.mark.parametrize("n,bpc", [(11, 4), (1027, 16)])
-def test_paged_tiles_bit_exact(shape, n, bpc):
-    L, l0, l1 = (3, 1, 3) if n < 100 else (1, 0, 1)
+def _gather_and_scatter(shape, L, l0, l1, n, bpc):
+    """Both directions compared whole; the scatter's walk."""
     bs = shape[0]
     NB = 2 * n + 5
     s, cache, mirror = _setup(shape, L, NB, 700 + n)
@@ -83,7 +73,25 @@ def test_paged_tiles_bit_exact(shape, n, bpc):
     kvx.kvx_scatter_blocks(cache, l0, l1, _bt(dst_ids), n, bpc * bs, out)
     kvx.kvx_check()
     oracle.scatter(s, *mirror, l0, l1, dst_ids, bpc * bs, expect)
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
+    return kvx.kvx_copy_walk(cache, l0, l1, n, bpc * bs, False)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"p{i}" for i in range(len(SHAPES))])
+@pytest.mark.parametrize("n,bpc", [(11, 4), (1027, 16)])
+def test_paged_tiles_bit_exact(shape, n, bpc):
+    walk = _gather_and_scatter(shape, *((3, 1, 3) if n < 100 else (2, 0, 2)), n, bpc)
+    slab = int(np.prod(shape))
+    small = slab <= 2048 or (shape[1] == 1 and slab <= 8192)
+    assert walk["ordered"] == (n >= 1024 and not small)
+
+
+@pytest.mark.parametrize("shape", [(16, 8, 128, 1), (16, 2, 256, 2), (64, 1, 128, 2)],
+                         ids=["two heads", "half rows", "four vectors"])
+def test_paged_tiles_in_pairs_of_slices_bit_exact(shape):
+    """Eight layers, 16 KiB slabs: both directions move slices 2 MiB apart together."""
+    walk = _gather_and_scatter(shape, 8, 0, 8, 1027, 16)
+    assert walk["ordered"] == 1 and walk["fronts"] == 2 and walk["pair_slices"] == 8
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=[f"p{i}" for i in range(len(SHAPES))])
@@ -113,7 +121,7 @@ def test_paged_tile_chunk_lists_bit_exact(shape):
     kvx.kvx_check()
     for (_, a, m), img in zip(refs, images):
         oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, img)
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
 
 
 MIXED = [
@@ -149,7 +157,7 @@ def test_keys_and_values_in_one_wave(shape):
         kvx.kvx_scatter_blocks(cache, 0, L, _bt(dst_ids), n, bpc * bs, out)
         kvx.kvx_check()
         oracle.scatter(s, *mirror, 0, L, dst_ids, bpc * bs, expect)
-        _same_cache(cache, mirror, L)
+        check_cache_equals(cache, mirror, L)
     per_block = oracle.packed_bytes(s, 0, L, 1)
     refs = [(i * per_block, i, 1) for i in range(n)]  # chunks of two blocks, half full
     out = torch.full((n * per_block,), 0xA5, dtype=torch.uint8, device=DEV)
@@ -160,4 +168,4 @@ def test_keys_and_values_in_one_wave(shape):
     kvx.kvx_scatter_chunks(cache, 0, L, _bt(dst_ids), n, kvx.chunk_refs(refs, DEV), n, 2 * bs, out)
     kvx.kvx_check()
     oracle.scatter(s, *mirror, 0, L, dst_ids, bs, want)
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)

@@ -11,9 +11,9 @@ import threading
 import numpy as np
 import pytest
 
-import kvsynth
 import oracle
-from kvtest_util import Filled, device_cache, first_mismatch, host_mirror, seeded_ids, to_host
+from kvtest_util import (cache_and_mirror, check_cache_equals, device_table, first_mismatch,
+                         seeded_ids, to_host)
 
 torch = pytest.importorskip("torch")
 import paper_2609_11744_amd as kvx  # noqa: E402
@@ -45,14 +45,13 @@ def _listed(case, table_len, n_chunks):
 
 
 def _bt(ids):
-    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(DEV)
+    return device_table(ids, DEV)
 
 
 def _setup(case, NB, seed):
     layout, L, bs, h, d, e = case[:6]
     s = oracle.Shape(L, NB, bs, h, d, e, layout)
-    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
-    return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
+    return (s, *cache_and_mirror(s, seed, DEV))
 
 
 def _refs(lengths, per_block, gap=16):
@@ -61,13 +60,6 @@ def _refs(lengths, per_block, gap=16):
         refs.append((off, at, m))
         at, off = at + m, off + m * per_block + gap
     return refs, at, off
-
-
-def _same_cache(cache, mirror, L):
-    torch.cuda.synchronize()
-    for l in range(L):
-        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
-        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
 
 
 def _want(s, mirror, L, ids, refs, size, bs):
@@ -97,7 +89,7 @@ def test_ragged_lists_bit_exact(case):
     kvx.kvx_check()
     for o, a, m in refs:
         oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, want[o:o + m * per_block])
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
 
 
 @pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[2], CASES[7], CASES[9]],

@@ -1,15 +1,16 @@
 """Slabs of at most 2 KiB, several of which one workgroup moves: the grouped
 kernels at the sizes where they can go wrong (one vector; groups that fill a
 workgroup and that leave lanes over; whole waves per slab; the largest grouped
-slab and the first one that is not), in image order, on the linear walk and in
-destination order, as chunk lists with short chunks, with bad block ids and bad
-references. Everything is compared whole with the oracle."""
+slab and the first one that is not), in image order, on the linear walk and, for
+the first that is not grouped, in destination order, as chunk lists with short
+chunks, with bad block ids and bad references. Everything is compared whole with the oracle."""
 import numpy as np
 import pytest
 
 import kvsynth
 import oracle
-from kvtest_util import Filled, device_cache, first_mismatch, host_mirror, seeded_ids, to_host
+from kvtest_util import (cache_and_mirror, check_cache_equals, device_table, first_mismatch,
+                         seeded_ids, to_host)
 
 torch = pytest.importorskip("torch")
 import paper_2609_11744_amd as kvx  # noqa: E402
@@ -41,21 +42,13 @@ SHAPES = [
 
 
 def _bt(ids):
-    return torch.from_numpy(np.ascontiguousarray(ids, dtype=np.int32)).to(DEV)
+    return device_table(ids, DEV)
 
 
 def _setup(shape, L, NB, seed):
     layout, bs, h, d, e = shape
     s = oracle.Shape(L, NB, bs, h, d, e, layout)
-    fill = Filled(seed, kvsynth.ROLE_SRC, kvsynth.MODE_RAW)
-    return s, device_cache(s, fill, DEV), host_mirror(s, fill, range(NB))
-
-
-def _same_cache(cache, mirror, L):
-    torch.cuda.synchronize()
-    for l in range(L):
-        assert np.array_equal(to_host(cache.k[l]), mirror[0][l]), f"K layer {l}"
-        assert np.array_equal(to_host(cache.v[l]), mirror[1][l]), f"V layer {l}"
+    return (s, *cache_and_mirror(s, seed, DEV))
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=[f"s{i}" for i in range(len(SHAPES))])
@@ -77,7 +70,11 @@ def test_small_slabs_bit_exact(shape, n, bpc):
     kvx.kvx_scatter_blocks(cache, l0, l1, _bt(dst_ids), n, bpc * bs, out)
     kvx.kvx_check()
     oracle.scatter(s, *mirror, l0, l1, dst_ids, bpc * bs, expect)
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
+    walk = kvx.kvx_copy_walk(cache, l0, l1, n, bpc * bs, False)
+    slab = int(np.prod(shape[1:]))
+    assert walk["ordered"] == (n >= 1024 and shape[0] == HND and slab > 2048)
+    assert walk["linear"] == (n >= 1024 and 4096 % slab == 0)
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=[f"s{i}" for i in range(len(SHAPES))])
@@ -107,7 +104,7 @@ def test_small_slab_chunk_lists_bit_exact(shape):
     kvx.kvx_check()
     for (_, a, m), img in zip(refs, images):
         oracle.scatter(s, *mirror, 0, L, dst_ids[a:a + m], m * bs, img)
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
 
 
 @pytest.mark.parametrize("shape", [SHAPES[3], SHAPES[4], SHAPES[12]], ids=["lane", "wave", "hnd"])
@@ -131,7 +128,7 @@ def test_small_slabs_skip_and_report_bad_ids_and_refs(shape):
     for i in good:
         oracle.scatter(s, *mirror, 0, L, ids[i:i + 1], bs,
                        img[i * per_block:(i + 1) * per_block])
-    _same_cache(cache, mirror, L)
+    check_cache_equals(cache, mirror, L)
     # a chunk list with one reference past the table: the others still move
     refs = [(c * bpc * per_block, c * bpc, bpc) for c in range(n // bpc)]
     refs[2] = (refs[2][0], n - 1, bpc)
