@@ -154,11 +154,13 @@ kvx_status kvx_scatter_blocks(const kvx_cache* cache, int32_t l0, int32_t l1,
                               const void* src, hipStream_t stream);
 
 /* How kvx_gather_blocks (to_packed = 1) or kvx_scatter_blocks (0) with these
- * arguments walks its work: the launcher's own choice, reported for tests and
- * measurement records. Pure host code: the cache's tensor pointers may be
- * NULL. A call moves work_items pieces of slabs, parts per slab (4 KiB pieces
- * with the default layout, heads with the others); a workgroup moves one piece,
- * or where pieces are small several, or a share of a large one. A scatter of
+ * arguments walks its work, for tests and measurement records: the order
+ * (ordered, linear, pair_slices, fronts) is the launcher's own choice. Pure host
+ * code: the cache's tensor pointers may be NULL. work_items and parts count the
+ * work, not the launch: a call moves work_items pieces of slabs, parts per slab
+ * (4 KiB pieces with the default layout, heads with the others), and its
+ * workgroups are cut otherwise where that is faster (several small slabs, several
+ * heads or a share of one, even shares of a slab). A scatter of
  * 1,024 blocks or more over more than one layer, in chunks of more than one
  * block, runs in ascending destination order (ordered = 1; block ids bucketed
  * by a small kernel first), except with slabs of at most 8 KiB in the default
@@ -230,6 +232,8 @@ typedef struct kvx_chunk_ref {
  * allocated and the host does not wait. A stream keeps its part; one without a part
  * takes the least recently used one and, on the device, waits for the list call
  * that had it, so list calls on up to four streams do not wait for each other.
+ * The copy is sized by table_len: a list whose chunks share table entries is
+ * copied in rounds, which can take a quarter longer than without the sharing.
  * Host-checkable errors as for kvx_gather_blocks (KVX_EINVAL), plus a launch
  * too large for 32-bit unit indexes (n_chunks * (l1 - l0) * 2 * blocks per
  * chunk >= 2^31). The refs live on the device and are checked by the kernel:

@@ -6,9 +6,10 @@
 // same order on both sides, so nothing is transposed and no LDS is used; of the
 // other cache layouts only paged attention goes through LDS (see move_tile).
 // A unit is a slab (layer, K|V, block) of `slab` bytes. With the default
-// layout one workgroup moves one part of a unit: 256 threads, one 16-byte
+// layout one workgroup moves one part of a unit: up to 256 threads, one 16-byte
 // vector each, so a part is 4 KiB (a 32 KiB slab is 8 parts; the last part of
-// a slab may be short). On this chip a copy moves measurably more bytes per
+// a slab may be short, and slabs a little over 4 or 8 KiB are cut evenly:
+// piece_vectors). On this chip a copy moves measurably more bytes per
 // second with one load and one store per thread in many short workgroups than
 // with several vectors per thread in fewer, longer ones (contiguous 4 GiB:
 // 83 % of peak against 77.5 % at 1024 threads x 2 vectors; the 80k gather
@@ -87,10 +88,11 @@ struct LayerPtrs {
 // Division by a divisor known only at run time, as a multiply: for d >= 2,
 // m = ceil(2^32 / d) and n / d = umulhi(n, m) whenever n * d < 2^32 (the
 // rounding error of m, below d, then moves n * m / 2^32 by less than 1/d);
-// m = 0 stands for d = 1. Every numerator here is an element or vector index
-// inside one head's part of a slab and every divisor a slab dimension; a
-// transposed slab is at most kMaxTransposedSlab (48 KiB) bytes, so both are
-// below 2^16.
+// m = 0 stands for d = 1. A numerator here is a vector or element index inside a
+// slab of a reordering layout (of at most 48 KiB) or of at most kGroupMaxVectors
+// vectors, or a thread of a workgroup, and a divisor a dimension of that slab: both
+// are below 2^16. Slabs of the default layout can be larger; their fields that do
+// not keep to this (v16, outer, n16) are set but not divided by.
 struct FastDiv {
   uint32_t d;
   uint32_t m;
@@ -241,9 +243,9 @@ __device__ __forceinline__ void move_piece(const v4u* __restrict__ s, v4u* __res
 // In every one of them a head's data is contiguous on the cache side (nh =
 // bs * v16 vectors), and on the packed side it is one v16-vector row per token
 // at stride prow = heads * v16.
-//   * HND: vectors move directly (no LDS). A workgroup writes 256 consecutive
-//     vectors of the destination slab and reads runs of v16 vectors (or the
-//     parts of them that its piece covers).
+//   * HND: vectors move directly (no LDS). A workgroup writes g.piece consecutive
+//     vectors of the destination slab (at most 256: piece_vectors) and reads runs
+//     of v16 vectors (or the parts of them that its piece covers).
 //   * paged attention: a workgroup moves a tile of about 256 vectors: whole
 //     neighbouring heads where they are small, and where a head is larger a
 //     run of at least 128 bytes of each of its tokens' rows (tile_geom). Either
@@ -327,8 +329,8 @@ __device__ __forceinline__ uint32_t hnd_source(uint32_t w, const SlabGeom& g) {
   return a * g.v16.d + b * g.src_step + dv;
 }
 
-// HND: move piece `part` of a slab: 256 consecutive vectors of the destination
-// (fewer in a slab's last piece).
+// HND: move piece `part` of a slab: g.piece consecutive vectors of the destination,
+// at most 256 (fewer in a slab's last piece).
 __device__ __forceinline__ void move_rows(const v4u* __restrict__ src, v4u* __restrict__ dst,
                                           uint32_t n16, const SlabGeom& g, uint32_t part) {
   const uint32_t w = part * g.piece + threadIdx.x;
@@ -681,8 +683,9 @@ __device__ __forceinline__ void move_tile(v4u* pv, v4u* pk, const SlabGeom& g, u
     });
 }
 
-// Move part `part` of one slab in the direction and layout of the kernel: a
-// 4 KiB piece with the default layout and HND, one tile with paged attention.
+// Move part `part` of one slab in the direction and layout of the kernel: a piece of
+// g.piece vectors (at most 256) with the default layout and HND, one tile with paged
+// attention.
 template <bool kToPacked, int kLayout, int kElem, bool kOne, int T, int V>
 __device__ __forceinline__ void move_unit(char* paged, char* pk, uint32_t n16, const SlabGeom& g,
                                           uint32_t kv, uint32_t part) {
@@ -963,9 +966,12 @@ __global__ void __launch_bounds__(kListThreads)
 // LDS phases the loop cost 8 to 25 % (8 x 128 dims, 1 GiB, uneven lists, gather /
 // scatter: bf16 389 / 398 us looped, 357 / 397 in two launches; 8-bit 423 / 510
 // and 372 / 402), around plain moves nothing. A list that does share pays for the
-// rounds: 16 requests of four shared 16-block chunks and one of their own, gathered,
-// padded / listed: 32 KiB slabs 877 / 848 us, paged attention 890 / 1098, 8-bit 928 /
-// 1178; 32 such requests of 4 KiB slabs, 80 layers, 572 / 626.
+// rounds, which the host cannot foresee (the lengths are in device memory): 16
+// requests of four shared 16-block chunks and 3 blocks of their own, 2.25 GB gathered,
+// padded / listed: 32 KiB slabs 763 / 845 us, paged attention 785 / 966; 32 such
+// requests of 4 KiB slabs, 80 layers, 1.4 GB, 502 / 576. Decoding a round's part while
+// the loads of the one before are in flight gained 1 to 5 % of that and lost 3 % with
+// 8-bit tiles.
 template <bool kToPacked, bool kLoop, int kLayout, int kElem, bool kOne, int T, int V>
 __global__ void __launch_bounds__(T)
     copy_list_kernel(LayerPtrs layers, const int32_t* __restrict__ block_table,
