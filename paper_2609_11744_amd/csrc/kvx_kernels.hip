@@ -831,7 +831,8 @@ __device__ __forceinline__ bool chunk_ref_ok(const kvx_chunk_ref& ref, const Chu
   return ref.n_blocks >= 1 && (uint32_t)ref.n_blocks <= g.bpc && ref.bt_offset >= 0 &&
          (int64_t)ref.bt_offset + ref.n_blocks <= (int64_t)g.table_len &&
          ref.packed_offset >= 0 && (ref.packed_offset & 15) == 0 &&
-         ref.packed_offset + (int64_t)g.lr2 * ref.n_blocks * (int64_t)g.slab <= g.packed_bytes;
+         ref.packed_offset <=  // a sum could wrap
+             g.packed_bytes - (int64_t)g.lr2 * ref.n_blocks * (int64_t)g.slab;
 }
 
 template <bool kToPacked, int kLayout, int kElem, bool kOne, int T, int V>

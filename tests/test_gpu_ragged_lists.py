@@ -159,6 +159,31 @@ def test_shared_entries_of_tiles_larger_than_the_second_launch():
     assert first_mismatch(to_host(out), want) is None
 
 
+@pytest.mark.parametrize("pad", [False, True], ids=["listed", "padded"])
+def test_references_at_the_end_of_64_bits_are_refused(pad):
+    """An offset to which the chunk's bytes cannot be added without wrapping."""
+    case = CASES[0]
+    _, L, bs, _, _, _, bpc, lengths, _ = case
+    lengths = [4] * 4 if pad else lengths
+    n = sum(lengths)
+    assert _listed(case, n, len(lengths)) != pad
+    s, cache, mirror = _setup(case, n, 970)
+    per_block = oracle.packed_bytes(s, 0, L, 1)
+    refs, table_len, size = _refs(lengths, per_block)
+    (ids,) = seeded_ids(970, n, n)
+    top = 2 ** 63 - 16
+    given = [(top - 64 * per_block * (i == 3), a, m) if i in (1, 3) else (o, a, m)
+             for i, (o, a, m) in enumerate(refs)]
+    out = torch.full((size,), 0xA5, dtype=torch.uint8, device=DEV)
+    kvx.kvx_gather_chunks(cache, 0, L, _bt(ids), table_len, kvx.chunk_refs(given, DEV), len(refs),
+                          bpc * bs, out)
+    with pytest.raises(kvx.KvxError) as e:
+        kvx.kvx_check()
+    assert e.value.status == kvx.KVX_EINVAL
+    good = [r for i, r in enumerate(refs) if i not in (1, 3)]
+    assert first_mismatch(to_host(out), _want(s, mirror, L, ids, good, size, bs)) is None
+
+
 def test_ragged_list_under_capture_replays_bit_exact():
     case = CASES[0]
     _, L, bs, _, _, _, bpc, lengths, _ = case
