@@ -59,13 +59,13 @@ KERNELS_SRC = [os.path.join(ROOT, "paper_2609_11744_amd", "csrc", f)
 # only for the kernel code they were taken on (kernels_sha256 below); otherwise the
 # bench reports traffic as null.
 GATHER_TRAFFIC = {
-    "kernels_sha256": "6475dd2e8ae523b3ea2a13426aaff85cb7a40b789e00ebb9abd9c0c58a1a5de7",
+    "kernels_sha256": "5f6f913f2aa6df0bb21fbe98a9404f5781edc34466b7884afc78a9f03ef41001",
     # cache layout -> (fetched, written) HBM bytes of the timed gather launch
     # at the default 80k-token workload: FETCH_SIZE KiB x 1.999988 (copy
     # calibration), WRITE_SIZE KiB x 1.0
-    "nhd": (10488801949, 10485760000),         # 5,121,514.9 / 10,240,000.0 KiB
-    "paged_attn": (10488988902, 10485760000),  # 5,121,607.8 / 10,240,000.0 KiB
-    "hnd": (10488820441, 10485760000),         # 5,121,525.2 / 10,240,000.0 KiB
+    "nhd": (10488838685, 10485760000),         # 5,121,532.9 / 10,240,000.0 KiB
+    "paged_attn": (10488992186, 10485760000),  # 5,121,608.4 / 10,240,000.0 KiB
+    "hnd": (10488852125, 10485760000),         # 5,121,539.4 / 10,240,000.0 KiB
 }
 
 
