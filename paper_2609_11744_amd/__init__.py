@@ -179,10 +179,11 @@ def _image_bytes(cache, l0, l1, n_blocks) -> int:
     without asking the library again for what only the cache's shape decides.
     Counted in Python's own integers: a NumPy or tensor scalar, which the library
     call takes too, would wrap in its 16 or 32 bits."""
-    try:
-        l0, l1, n_blocks = operator.index(l0), operator.index(l1), operator.index(n_blocks)
-    except TypeError:  # the library call converts it, or refuses it
-        return max(kvx_packed_bytes(cache, l0, l1, n_blocks), 0)
+    if not type(l0) is type(l1) is type(n_blocks) is int:
+        try:
+            l0, l1, n_blocks = operator.index(l0), operator.index(l1), operator.index(n_blocks)
+        except TypeError:  # the library call converts it, or refuses it
+            return max(kvx_packed_bytes(cache, l0, l1, n_blocks), 0)
     if cache._layer_block is None:
         one = kvx_packed_bytes(cache, 0, 1, 1)
         pieces = kvx_copy_walk(cache, 0, 1, 1, cache.block_size, True)["work_items"] if one > 0 else 0
