@@ -100,7 +100,7 @@ namespace {
 // blocks), 354 / 354 (32 layers, 4,096) and 94 / 91 (1,100), 8 KiB 637 / 632 and
 // 344 / 340, 2 KiB 215 / 210 and 351 / 343, 1 KiB 176 / 167. Over 36 calls of 1 and
 // 2 KiB slabs, 16 to 80 layers, six pairs each, unheld took 0.953 to 1.023 of the time
-// held, 0.986 on the mean: where the buffers land decides, not the shape.
+// held, 0.988 on the mean: where the buffers land decides, not the shape.
 bool small_rows(int64_t slab, int layout, int32_t heads) {
   return slab <= 16 * (int64_t)kGroupMaxVectors ||
          (slab <= 8192 && (layout == KVX_LAYOUT_NHD || heads == 1));
